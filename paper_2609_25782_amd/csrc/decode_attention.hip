@@ -32,7 +32,8 @@
 // whose base is the page and whose size is its two tiles: an out-of-range page
 // id becomes a zero-sized resource, reads return 0 and the row is flagged NaN.
 // Each wave keeps a ring of page buffers in registers: while one page is
-// computed, the loads of the next ring - 1 pages are in flight.
+// computed, the loads of the next ring - 1 pages are in flight, whichever rows
+// they belong to.
 
 #include "device_common.h"
 #include "kernels.h"
@@ -108,13 +109,16 @@ struct PageSrc {
     unsigned num_hot = 0, num_cold = 0, num_stage = 0;
 };
 
-// Page ids are wave-uniform, so the tier choice is scalar.  An id outside its
-// pool (or a negative entry) reads nothing: the buffer resource gets no records
-// and the row is marked bad (NaN).
-template <int D, bool BF16, bool TIERED>
-__device__ __forceinline__ void load_page(PageRegs<D, BF16>& r, const PageSrc& ps, int pid, bool& bad,
-                                          unsigned koff, unsigned voff) {
-    using S = Shape<D, BF16>;
+// A (page, KV head)'s two tiles.  Page ids are wave-uniform, so the tier choice
+// is scalar.  An id outside its pool (or a negative entry) reads nothing: the
+// buffer resource gets no records and the row is marked bad (NaN).
+struct PageAddr {
+    const char* base;
+    bool ok;
+};
+
+template <bool TIERED>
+__device__ __forceinline__ PageAddr page_addr(const PageSrc& ps, int pid, unsigned head_off) {
     const char* lh_base = ps.hot;
     int64_t stride = ps.hot_stride;
     unsigned n = ps.num_hot;
@@ -135,20 +139,34 @@ __device__ __forceinline__ void load_page(PageRegs<D, BF16>& r, const PageSrc& p
         }
     }
     const bool ok = id < n;
-    bad |= !ok;
-    const char* base = lh_base + static_cast<int64_t>(ok ? id : 0) * stride;
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), static_cast<short>(0),
-                                          ok ? 2 * S::kTile : 0, kRsrcWord3);
+    return PageAddr{lh_base + static_cast<int64_t>(ok ? id : 0) * stride + head_off, ok};
+}
+
+template <int D, bool BF16>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t page_rsrc(const PageAddr& p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p.base), static_cast<short>(0),
+                                             p.ok ? 2 * Shape<D, BF16>::kTile : 0, kRsrcWord3);
+}
+
+// Offsets past the instruction's 12 bits go into the scalar offset: one VGPR of
+// offsets for all K loads and one for all V loads.
+template <int D, bool BF16>
+__device__ __forceinline__ void load_page_k(PageRegs<D, BF16>& r, __amdgpu_buffer_rsrc_t rs, unsigned koff) {
 #pragma unroll
-    for (int i = 0; i < S::kKLoads; ++i)
-        r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, koff + 1024u * i, 0, HCK_DECODE_LOAD_AUX);
+    for (int i = 0; i < Shape<D, BF16>::kKLoads; ++i)
+        r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, koff + 1024u * (i % 4), 4096 * (i / 4), HCK_DECODE_LOAD_AUX);
+}
+
+template <int D, bool BF16>
+__device__ __forceinline__ void load_page_v(PageRegs<D, BF16>& r, __amdgpu_buffer_rsrc_t rs, unsigned voff) {
+    using S = Shape<D, BF16>;
 #pragma unroll
     for (int c = 0; c < S::kChunks; ++c) {
         if constexpr (BF16)
-            r.v[c] = __builtin_amdgcn_raw_buffer_load_b64(rs, voff + S::kTile + 512u * c, 0, HCK_DECODE_LOAD_AUX);
+            r.v[c] = __builtin_amdgcn_raw_buffer_load_b64(rs, voff + 512u * c, S::kTile, HCK_DECODE_LOAD_AUX);
         else
-            r.v[c] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + S::kTile + 1024u * c, 0, HCK_DECODE_LOAD_AUX);
+            r.v[c] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 1024u * (c % 4), S::kTile + 4096 * (c / 4),
+                                                           HCK_DECODE_LOAD_AUX);
     }
 }
 
@@ -406,168 +424,232 @@ __device__ void combine_segment(const DecodeArgs& a, int b, int g, int64_t u_a, 
         const int idx = it * kWave + lane;
         if (idx < items) {
             const int h = idx / kQuads, quad = idx % kQuads;
-            const f32x4 res = invalid ? f32x4{nan, nan, nan, nan} : acc[it] / den[it];
+            const f32x4 res = invalid ? f32x4{nan, nan, nan, nan} : BF16 ? acc[it] * (1.0f / den[it]) : acc[it] / den[it];
             store_quad<D, BF16>(a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad,
                                 res);
         }
     }
 }
 
-// Fused append (paged_decode_attention_append): the piece holding a row's last
-// page first writes the row's new token, k_new / v_new row b for this wave's
-// KV head, into that page at slot (L - 1) % 16, then orders those stores before
-// its own loads of the page (the same wave is the only reader of that page's
-// tiles for this KV head in the launch).  Rows with L <= 0 or an invalid L, and
-// tail entries that name no page (or a staging slot), write nothing.
-template <int D, bool BF16, bool TIERED>
-__device__ __forceinline__ void append_new_token(const DecodeArgs& a, const PageSrc& ps, const int32_t* row,
-                                                 const Piece& pc, int nb, int seq_len, int lane) {
-    using S = Shape<D, BF16>;
-    if (!a.k_new || pc.p1 != nb || seq_len <= 0 || a.seq_lens[pc.b] != seq_len) return;
-    unsigned id = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(row[nb - 1]));
-    const char* base = ps.hot;
-    int64_t stride = ps.hot_stride;
-    unsigned n = ps.num_hot;
-    if constexpr (TIERED) {
-        const unsigned tag = id >> 29;  // 0 hot, 2 cold; a staged slot is a copy, not the page
-        id &= static_cast<unsigned>(kPageIdMask);
-        if (tag == 2) {
-            base = ps.cold;
-            stride = ps.cold_stride;
-            n = ps.num_cold;
-        } else if (tag != 0) {
-            n = 0;
+// ---------------------------------------------------------------------------
+// The unit stream.  A wave's units [u0, u1) are consecutive pages of one or
+// more segments (row, head group).  Lane j of a chunk register holds unit
+// base + j: its page id and a word saying which row and head group it belongs
+// to and where it stands in its segment, so the loop needs one readlane per
+// word and no arithmetic on rows.
+constexpr unsigned kUnitRowMask = (1u << 13) - 1;  // row (kMaxDecodeBatch = 8192)
+constexpr int kUnitGroupShift = 13;                // head group, 4 bits
+constexpr unsigned kUnitFirst = 1u << 17;          // first unit of a piece: new queries, new accumulators
+constexpr unsigned kUnitLast = 1u << 18;           // last unit of a piece: its result goes out
+constexpr unsigned kUnitSegFirst = 1u << 19;       // the segment's first page
+constexpr unsigned kUnitSegLast = 1u << 20;        // the segment's last page (the row's tail page)
+constexpr unsigned kUnitNone = 1u << 27;           // past the end of the wave's units
+// set by the load stage:
+constexpr int kUnitTailShift = 21;                 // tokens of the page - 1, 4 bits (15 except on tail pages)
+constexpr unsigned kUnitRowInvalid = 1u << 25;     // with kUnitSegLast: the length does not fit the table row
+constexpr unsigned kUnitBad = 1u << 26;            // the page id names no page
+constexpr unsigned kUnitQueries = 1u << 28;        // the piece's queries were loaded with this page
+constexpr unsigned kUnitToken = 1u << 29;          // the row's new token was loaded with this page
+static_assert(kMaxDecodeBatch <= (1 << 13), "row bits of a unit word");
+
+struct UnitChunk {
+    int pid;
+    int len;  // the row's length
+    unsigned word;
+};
+
+// Where a chunk starts: unit `off` of row b's units (heads * pages of them).
+struct UnitPos {
+    int b;
+    unsigned off;
+};
+
+// Position of unit u (wave-uniform): a 64-way search of the row prefix, one LDS
+// read per level.
+__device__ __forceinline__ UnitPos unit_pos(const int32_t* s_pref, int batch, int heads, int64_t u, int lane) {
+    const int64_t target = heads == 1 ? u
+                           : (u >> 32) == 0 ? static_cast<int64_t>(static_cast<unsigned>(u) / static_cast<unsigned>(heads))
+                                            : u / heads;
+    int lo = 0, n = batch;  // the row is in [lo, lo + n)
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const int i = lane * step;
+        const bool le = i < n && s_pref[lo + i] <= target;
+        const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le)) - 1;  // row lo is always <= target
+        lo += c * step;
+        n = n - c * step < step ? n - c * step : step;
+    }
+    UnitPos p;
+    p.b = lo;
+    p.off = static_cast<unsigned>(u - static_cast<int64_t>(lds_uniform(s_pref + lo)) * heads);
+    return p;
+}
+
+// Units [at, at + kUnits) of the stream, one per lane; `left` units remain from the
+// chunk's start (lanes past them get kUnitNone).  Rows after the chunk's first are found by a
+// galloping search: consecutive units are in the same or the next rows.
+// A row has at most 2^27 pages (lengths are int32) and 16 head groups, so the
+// offsets within a row fit 32 bits; `at` moves on to the next chunk.
+template <int kUnits>
+__device__ __forceinline__ UnitChunk load_units(const DecodeArgs& a, const int32_t* s_pref, int heads, UnitPos& at,
+                                                int64_t left, bool worker_start, int lane) {
+    const unsigned off = at.off + lane;
+    const int32_t p0 = lds_uniform(s_pref + at.b);
+    const bool in = lane < left && lane < kUnits;
+    const int32_t q = static_cast<int32_t>(heads == 1 ? off : off / static_cast<unsigned>(heads));
+    int b = at.b, step = 1;
+    if (in) {
+        while (b + step < a.batch && s_pref[b + step] - p0 <= q) {
+            b += step;
+            step <<= 1;
         }
+        for (step >>= 1; step > 0; step >>= 1)
+            if (b + step < a.batch && s_pref[b + step] - p0 <= q) b += step;
     }
-    if (id >= n) return;
-    char* lh = const_cast<char*>(base) + static_cast<int64_t>(id) * stride;
-    const int slot = (seq_len - 1) % kPageTokens;
-    const int64_t src = (static_cast<int64_t>(pc.b) * a.num_kv_heads + pc.g) * D * S::kElt;
-    const char* ks = static_cast<const char*>(a.k_new) + src;
-    const char* vs = static_cast<const char*>(a.v_new) + src;
-    constexpr int x = 16 / S::kElt;  // elements per 16-byte group of the K tile
-    if (lane < D / x)
-        *reinterpret_cast<u32x4*>(lh + (static_cast<int64_t>(lane) * kPageTokens + slot) * 16) =
-            *reinterpret_cast<const u32x4*>(ks + 16 * lane);
-    for (int d = lane; d < D; d += kWave) {
-        char* vd = lh + S::kTile + (static_cast<int64_t>(d) * kPageTokens + slot) * S::kElt;
-        if constexpr (BF16)
-            *reinterpret_cast<unsigned short*>(vd) = reinterpret_cast<const unsigned short*>(vs)[d];
-        else
-            *reinterpret_cast<unsigned*>(vd) = reinterpret_cast<const unsigned*>(vs)[d];
-    }
-    // Other lanes of this wave read these bytes back with the page's loads.  A
-    // workgroup-scope release/acquire orders that in the memory model; waiting
-    // for the stores to be acknowledged makes the order independent of how the
-    // L1 treats the nontemporal loads (once per row's tail page: negligible).
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int32_t first = s_pref[b];
+    const unsigned nb = static_cast<unsigned>(s_pref[b + 1] - first);
+    const unsigned rel = off - static_cast<unsigned>(heads) * static_cast<unsigned>(first - p0);
+    const unsigned g = heads == 1 || !in ? 0u : rel / nb;
+    const unsigned p = in ? rel - g * nb : 0u;
+    // no branch around the loads (lanes past the end read their row's first
+    // entry): they then land in the chunk's registers without a copy and its wait
+    UnitChunk c;
+    c.pid = a.page_table[static_cast<int64_t>(b) * a.pt_stride + p];
+    c.len = a.seq_lens[b];
+    unsigned word = static_cast<unsigned>(b) | (g << kUnitGroupShift);
+    if (p == 0) word |= kUnitFirst | kUnitSegFirst;
+    if (worker_start && lane == 0) word |= kUnitFirst;
+    if (p == nb - 1) word |= kUnitLast | kUnitSegLast;
+    if (lane == left - 1) word |= kUnitLast;
+    c.word = in ? word : kUnitNone;
+    at.b = __builtin_amdgcn_readlane(b, kUnits - 1);
+    at.off = __builtin_amdgcn_readlane(rel, kUnits - 1) + 1;
+    return c;
 }
 
-__device__ __forceinline__ int load_ids(const int32_t* __restrict__ row, int first, int end,
-                                        int lane) {
-    const int i = first + lane;
-    return i < end ? row[i] : -1;
-}
+// The V part of a row's new token (fused append): the element of each 16-dim
+// chunk that the lane's V registers of the tail page take.
+template <int D, bool BF16>
+struct TokenV {
+    unsigned v[Shape<D, BF16>::kChunks];
+};
 
-// Process pages [p0, p1) of row b, KV head g, and write the partial to its slot.
-// R page buffers form a ring: while one page is computed, the next R - 1 are
-// in flight.
-template <int D, bool BF16, int R, bool TIERED>
-__device__ void run_piece(const DecodeArgs& a, const Piece& pc, int nb, int seq_len, bool row_invalid,
-                          int lane, int64_t seg_first_unit, int64_t total_units) {
+template <int D, bool BF16>
+__device__ __forceinline__ void load_queries(u32x4* __restrict__ q, const DecodeArgs& a, int b, int g,
+                                             int lane) {
     using S = Shape<D, BF16>;
-    const int h = lane & 15, qg = lane >> 4;
-    const bool hvalid = h < a.group;
-    SegmentState<D, BF16> st;
-    {
-        const char* qrow = static_cast<const char*>(a.q) +
-                           (static_cast<int64_t>(pc.b) * a.num_q_heads + pc.g * a.group +
-                            (hvalid ? h : 0)) * D * S::kElt;
+    const int64_t row = static_cast<int64_t>(b) * a.num_q_heads + g * a.group;
+    // lanes of head slots past the group read past the resource: zeros
+    const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(static_cast<const char*>(a.q) + row * (D * S::kElt)), static_cast<short>(0),
+        a.group * D * S::kElt, kRsrcWord3);
+    const unsigned off = static_cast<unsigned>((lane & 15) * D * S::kElt + 16 * (lane >> 4));
+#pragma unroll
+    for (int i = 0; i < S::kKLoads; ++i) q[i] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + 64u * i, 0, 0);
+}
+
+template <int D, bool BF16>
+__device__ __forceinline__ void load_token_v(TokenV<D, BF16>& t, const DecodeArgs& a, int b, int g, int lane) {
+    const int64_t src = (static_cast<int64_t>(b) * a.num_kv_heads + g) * D + (lane & 15);
+#pragma unroll
+    for (int c = 0; c < Shape<D, BF16>::kChunks; ++c) {
+        if constexpr (BF16)
+            t.v[c] = static_cast<const unsigned short*>(a.v_new)[src + 16 * c];
+        else
+            t.v[c] = static_cast<const unsigned*>(a.v_new)[src + 16 * c];
+    }
+}
+
+// Fused append (paged_decode_attention_append): row b's new token, k_new /
+// v_new row b, is token L - 1 of the row, slot (L - 1) % 16 of its tail page.
+// The lanes that hold the slot's K take it from k_new instead of the page, and
+// the lanes that hold its V put the new element in place of the page's, which
+// may be the old or the new one by then; the same lanes store both to the page.
+// So the append adds no wait.  No other wave reads that (page, KV head) in the
+// launch.  Writing the token first and reading it back cost a load, a store and
+// its acknowledgement before the row's first page load.
+template <int D, bool BF16>
+__device__ __forceinline__ void load_tail_k(PageRegs<D, BF16>& pg, const char* page, const DecodeArgs& a, int b, int g,
+                                            int slot, bool ok, unsigned koff, int lane) {
+    using S = Shape<D, BF16>;
+    const char* ks = static_cast<const char*>(a.k_new) + (static_cast<int64_t>(b) * a.num_kv_heads + g) * D * S::kElt;
+    // a page id that names no page: nothing of it is read (the row is NaN)
+    const bool own = (lane & 15) == slot || !ok;
+    const char* p = own ? ks + 16 * (lane >> 4) : page + koff;
+    const int step = own ? 64 : 1024;
+#pragma unroll
+    for (int i = 0; i < S::kKLoads; ++i)
+        pg.k[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + step * i));
+}
+
+template <int D, bool BF16>
+__device__ __forceinline__ void append_in_place(PageRegs<D, BF16>& pg, const TokenV<D, BF16>& t,
+                                                __amdgpu_buffer_rsrc_t page, int slot, unsigned koff, unsigned voff,
+                                                int lane) {
+    using S = Shape<D, BF16>;
+    if ((lane & 15) == slot) {
 #pragma unroll
         for (int i = 0; i < S::kKLoads; ++i)
-            st.q[i] = hvalid ? *reinterpret_cast<const u32x4*>(qrow + 16 * (4 * i + qg))
-                             : u32x4{0u, 0u, 0u, 0u};
+            __builtin_amdgcn_raw_buffer_store_b128(pg.k[i], page, koff + 1024u * (i % 4), 4096 * (i / 4), 0);
     }
+    if ((lane >> 4) == slot >> 2) {
+        const int j = slot & 3;
 #pragma unroll
-    for (int c = 0; c < S::kChunks; ++c) st.o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    st.m = -INFINITY;
-    st.l = 0.f;
-    bool bad = false;
-
-    const int32_t* row = a.page_table + static_cast<int64_t>(pc.b) * a.pt_stride;
-    const int64_t head_off = static_cast<int64_t>(pc.g) * 2 * S::kTile;
-    PageSrc ps;
-    ps.hot = a.hot + head_off;
-    ps.hot_stride = a.hot_stride;
-    ps.num_hot = static_cast<unsigned>(a.num_pages);
-    if constexpr (TIERED) {
-        ps.cold = a.cold + head_off;
-        ps.cold_stride = a.cold_stride;
-        ps.stage = a.stage + head_off;
-        ps.slice_bytes = a.slice_bytes;
-        ps.num_cold = static_cast<unsigned>(a.num_cold_pages);
-        ps.num_stage = static_cast<unsigned>(a.num_stage_slots);
-    }
-    append_new_token<D, BF16, TIERED>(a, ps, row, pc, nb, seq_len, lane);
-    const unsigned koff = 16u * lane;
-    const unsigned voff = BF16 ? (32u * (lane & 15) + 8u * qg) : (64u * (lane & 15) + 16u * qg);
-    // valid tokens of the row's last page (16 when full)
-    const int tail_valid = seq_len - kPageTokens * (nb - 1);
-
-    int ids_cur = load_ids(row, pc.p0, pc.p1, lane);
-    int ids_nxt = load_ids(row, pc.p0 + kWave, pc.p1, lane);
-    int cur_chunk = 0;
-    auto pid_at = [&](int i) -> int {
-        const int rel = i - pc.p0;
-        const int cc = rel >> 6;
-        if (cc != cur_chunk) {
-            ids_cur = ids_nxt;
-            cur_chunk = cc;
-            ids_nxt = load_ids(row, pc.p0 + kWave * (cc + 1), pc.p1, lane);
-        }
-        return __builtin_amdgcn_readlane(ids_cur, rel & 63);
-    };
-
-    PageRegs<D, BF16> buf[R];
+        for (int c = 0; c < S::kChunks; ++c) {
+            if constexpr (BF16) {
+                const unsigned shift = (j & 1) * 16u, keep = ~(0xFFFFu << shift);
+                const unsigned put = t.v[c] << shift;
+                if (j >> 1)
+                    pg.v[c][1] = (pg.v[c][1] & keep) | put;
+                else
+                    pg.v[c][0] = (pg.v[c][0] & keep) | put;
+                __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(t.v[c]), page,
+                                                      voff + 2u * j + 512u * c, S::kTile, 0);
+            } else {
 #pragma unroll
-    for (int r = 0; r < R - 1; ++r)
-        if (pc.p0 + r < pc.p1)
-            load_page<D, BF16, TIERED>(buf[r], ps, pid_at(pc.p0 + r), bad, koff, voff);
-    for (int i = pc.p0; i < pc.p1; i += R) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int ip = i + r;
-            if (ip < pc.p1) {
-                const int ahead = ip + R - 1;
-                if (ahead < pc.p1)
-                    load_page<D, BF16, TIERED>(buf[(r + R - 1) % R], ps, pid_at(ahead), bad, koff, voff);
-                compute_page<D, BF16>(st, buf[r], ip == nb - 1 ? tail_valid : kPageTokens,
-                                      a.scale_log2, qg);
+                for (int e = 0; e < 4; ++e)
+                    if (e == j) pg.v[c][e] = t.v[c];
+                __builtin_amdgcn_raw_buffer_store_b32(t.v[c], page, voff + 4u * j + 1024u * (c % 4),
+                                                      S::kTile + 4096 * (c / 4), 0);
             }
         }
     }
+}
 
+// A piece's result: the output rows themselves when the piece is its whole
+// segment, else a partial (running max, weight sum, unnormalised output).
+template <int D, bool BF16, bool FUSED>
+__device__ __forceinline__ void finish_piece(const DecodeArgs& a, SegmentState<D, BF16>& st, unsigned word,
+                                             bool whole, bool bad, int worker, int heads, int w_in, int lane) {
+    using S = Shape<D, BF16>;
+    const int h = lane & 15, qg = lane >> 4;
+    const bool hvalid = h < a.group;
+    const int b = static_cast<int>(word & kUnitRowMask), hg = static_cast<int>((word >> kUnitGroupShift) & 15u);
+    const int g = hg * a.group_waves + w_in;
     float l = wave_sum_4(st.l);
     if (bad) l = __builtin_nanf("");
-    if (pc.p0 == 0 && pc.p1 == nb) {
-        // The piece is the whole segment: its normalised result is the output.
-        // (o + 0) / l is what merging this one partial gives, bit for bit.
+    if (whole) {
+        // (o + 0) / l is what merging this one partial gives.  A head's lanes
+        // share l, so bf16 results take one division and multiply by it: the
+        // last float32 bit is far below bf16's rounding.
         if (hvalid) {
             const float nan = __builtin_nanf("");
-            const int64_t orow = (static_cast<int64_t>(pc.b) * a.num_q_heads + pc.g * a.group + h) * D + 4 * qg;
+            const bool row_invalid = (word & kUnitRowInvalid) != 0;
+            const int64_t orow = (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * qg;
+            const float inv = 1.0f / l;
 #pragma unroll
-            for (int c = 0; c < S::kChunks; ++c)
-                store_quad<D, BF16>(a, orow + 16 * c,
-                                    row_invalid ? f32x4{nan, nan, nan, nan} : (st.o[c] + 0.f) / l);
+            for (int c = 0; c < S::kChunks; ++c) {
+                const f32x4 res = BF16 ? (st.o[c] + 0.f) * inv : (st.o[c] + 0.f) / l;
+                store_quad<D, BF16>(a, orow + 16 * c, row_invalid ? f32x4{nan, nan, nan, nan} : res);
+            }
         }
         return;
     }
     if (hvalid) {
-        float* po = a.part_o + (static_cast<int64_t>(pc.slot) * a.group + h) * D + 4 * qg;
-        float* pml = a.part_ml + static_cast<int64_t>(pc.slot) * 2 * a.group;
-        if (a.fused) {
+        const int64_t slot = (static_cast<int64_t>(worker) + static_cast<int64_t>(b) * heads + hg) * a.group_waves + w_in;
+        float* po = a.part_o + (slot * a.group + h) * D + 4 * qg;
+        float* pml = a.part_ml + slot * 2 * a.group;
+        if constexpr (FUSED) {
             const PartialsRsrc pr(a);
 #pragma unroll
             for (int c = 0; c < S::kChunks; ++c) pr.store4(po + 16 * c, st.o[c]);
@@ -584,22 +666,212 @@ __device__ void run_piece(const DecodeArgs& a, const Piece& pc, int nb, int seq_
             }
         }
     }
-    if (a.fused) {
-        // The wave that delivers the last partial of (b, g) merges them all.
-        const SegWaves sw = seg_waves(seg_first_unit, nb, total_units, a.waves / a.group_waves);
-        int32_t* cnt = a.counters + pc.b * a.num_kv_heads + pc.g;
+}
+
+// The segments (b * heads + head group) that a worker shares with others, or
+// -1: the one its range starts inside of and finishes, and the one it does not
+// finish, which it may also have started (it then is the first of that
+// segment's workers).
+struct SplitEnds {
+    int first = -1, last = -1;
+    bool last_starts = false;
+};
+
+// Fused merge: this wave's partials of the shared segments are stored; the wave
+// that delivers a segment's last partial for its KV head merges them all.  The
+// partials went out as device-scope stores: once they are acknowledged they are
+// visible to every XCD, and the merging wave reads them back with device-scope
+// loads.  Arrivals wait for the end of the worker's range, so that no ring is
+// drained for them.
+template <int D, bool BF16>
+__device__ void merge_ends(const DecodeArgs& a, const int32_t* s_pref, const SplitEnds& ends, int heads, int w_in,
+                           int64_t total_units, int lane) {
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll 1
+    for (int e = 0; e < 2; ++e) {
+        const int seg = e ? ends.last : ends.first;
+        if (seg < 0) continue;
+        const int b = seg / heads, hg = seg % heads, g = hg * a.group_waves + w_in;
+        const int nb = lds_uniform(s_pref + b + 1) - lds_uniform(s_pref + b);
+        const int64_t seg_first = static_cast<int64_t>(lds_uniform(s_pref + b)) * heads + static_cast<int64_t>(hg) * nb;
+        const SegWaves sw = seg_waves(seg_first, nb, total_units, a.waves / a.group_waves);
+        int32_t* cnt = a.counters + b * a.num_kv_heads + g;
         int prev = 0;
-        // The partials went out as device-scope stores: once this wave's are
-        // acknowledged they are visible to every XCD, and the merging wave
-        // reads them back with device-scope loads.
-        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (lane == 0) prev = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         prev = __builtin_amdgcn_readfirstlane(__shfl(prev, 0));
         if (prev + 1 == sw.pieces) {
-            combine_segment<D, BF16>(a, pc.b, pc.g, seg_first_unit, nb, total_units, lane);
+            combine_segment<D, BF16>(a, b, g, seg_first, nb, total_units, lane);
             if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next call
         }
     }
+}
+
+// Process units [u0, u1) of `worker`, KV head w_in of each unit's head group.
+// R page buffers form a ring: step s issues unit s's loads and computes unit
+// s - (R - 1), so R - 1 pages are in flight behind the one computed, across the
+// ends of segments too: a new row costs its queries' registers and the old
+// row's output, not a drained ring.  Every step issues exactly one page's loads
+// (past the end with a resource of no records, which fetches nothing) and the
+// loops have no exit inside a round of R steps, so that the compiler's waits
+// count just the pages ahead: with the loads under a condition, as with an
+// early exit, they waited for nearly all of them.  A piece's queries, and the V
+// of a tail page's new token (fused append), are loaded ahead of their page into
+// one set of registers each; where rows are so short that the set is still in
+// use, they are loaded when their page is computed.
+// Measured against one drained ring, row search and 64-bit division per piece
+// (whole calls): 11 rows of up to 4K tokens, 16 heads of 64 dims, 33.2 -> 25.2
+// us; 1,024 rows of 512 tokens 196 -> 187 us; 32 rows of 8K-32K tokens 211.8 ->
+// 208.9 us (6.70 TB/s); a captured 48-layer step of 8 x 2K tokens with the fused
+// append 955 -> 848 us.
+template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND>
+__device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_t* s_pref, int64_t u0, int64_t u1,
+                                               int worker, int heads, int w_in, int lane) {
+    using S = Shape<D, BF16>;
+    constexpr int kChunk = kWave / R * R;  // units per chunk: whole rounds of the ring
+    SplitEnds ends;
+    if (u1 <= u0) return ends;
+    PageSrc ps;
+    ps.hot = a.hot;
+    ps.hot_stride = a.hot_stride;
+    ps.num_hot = static_cast<unsigned>(a.num_pages);
+    if constexpr (TIERED) {
+        ps.cold = a.cold;
+        ps.cold_stride = a.cold_stride;
+        ps.stage = a.stage;
+        ps.slice_bytes = a.slice_bytes;
+        ps.num_cold = static_cast<unsigned>(a.num_cold_pages);
+        ps.num_stage = static_cast<unsigned>(a.num_stage_slots);
+    }
+    const int qg = lane >> 4;
+    const unsigned koff = 16u * lane;
+    const unsigned voff = BF16 ? (32u * (lane & 15) + 8u * qg) : (64u * (lane & 15) + 16u * qg);
+
+    PageRegs<D, BF16> ring[R];
+    unsigned word[R];
+    int pid[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        word[r] = kUnitNone;
+        pid[r] = -1;
+    }
+    u32x4 q_next[S::kKLoads];
+    TokenV<D, BF16> token;
+    bool q_held = false, token_held = false;
+    auto group_of = [&](unsigned w) { return static_cast<int>((w >> kUnitGroupShift) & 15u) * a.group_waves + w_in; };
+    // the row takes a new token here: its tail page, and its length fits the table row
+    auto takes_token = [](unsigned w) { return (w & (kUnitSegLast | kUnitRowInvalid)) == kUnitSegLast; };
+
+    auto issue = [&](int r, const UnitChunk& c, int j) __attribute__((always_inline)) {
+        pid[r] = __builtin_amdgcn_readlane(c.pid, j);
+        unsigned w = __builtin_amdgcn_readlane(c.word, j);
+        unsigned tail = kPageTokens - 1;
+        if (w & kUnitSegLast) {
+            const int len = __builtin_amdgcn_readlane(c.len, j);
+            if (static_cast<int64_t>(len) > kPageTokens * a.pt_stride)
+                w |= kUnitRowInvalid;
+            else
+                tail = static_cast<unsigned>(len - 1) % kPageTokens;
+        }
+        w |= tail << kUnitTailShift;
+        const int b = static_cast<int>(w & kUnitRowMask), g = group_of(w);
+        PageAddr page = page_addr<TIERED>(ps, pid[r], g * 2u * S::kTile);
+        if (!page.ok) w |= kUnitBad;
+        if (w & kUnitNone) page.ok = false;
+        if ((w & kUnitFirst) && !q_held) {
+            load_queries<D, BF16>(q_next, a, b, g, lane);
+            w |= kUnitQueries;
+            q_held = true;
+        }
+        const bool token_here = APPEND && takes_token(w) && !(w & kUnitNone);
+        if (token_here && !token_held) {
+            load_token_v<D, BF16>(token, a, b, g, lane);
+            w |= kUnitToken;
+            token_held = true;
+        }
+        const __amdgpu_buffer_rsrc_t rs = page_rsrc<D, BF16>(page);
+        if (token_here)
+            load_tail_k<D, BF16>(ring[r], page.base, a, b, g, static_cast<int>(tail), page.ok, koff, lane);
+        else
+            load_page_k<D, BF16>(ring[r], rs, koff);
+        load_page_v<D, BF16>(ring[r], rs, voff);
+        word[r] = w;
+    };
+
+    SegmentState<D, BF16> st;
+    bool bad = false, seg_first = false;
+    // What a unit needs besides its page, taken before the step's own loads go
+    // out: those may load the next queries or token into the same registers.
+    auto begin = [&](int r) __attribute__((always_inline)) {
+        const unsigned w = __builtin_amdgcn_readfirstlane(word[r]);
+        if (w & kUnitNone) return;
+        const int b = static_cast<int>(w & kUnitRowMask), g = group_of(w);
+        if (w & kUnitFirst) {
+            if (w & kUnitQueries) {
+#pragma unroll
+                for (int i = 0; i < S::kKLoads; ++i) st.q[i] = q_next[i];
+                q_held = false;
+            } else {  // q_next holds a later piece's
+                load_queries<D, BF16>(st.q, a, b, g, lane);
+                // waited for here, so that the usual way keeps its pages in flight
+#pragma unroll
+                for (int i = 0; i < S::kKLoads; ++i) __asm__ volatile("" : "+v"(st.q[i]));
+            }
+#pragma unroll
+            for (int c = 0; c < S::kChunks; ++c) st.o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            st.m = -INFINITY;
+            st.l = 0.f;
+            bad = false;
+            seg_first = (w & kUnitSegFirst) != 0;
+        }
+        if (APPEND && takes_token(w)) {
+            const __amdgpu_buffer_rsrc_t page = page_rsrc<D, BF16>(
+                page_addr<TIERED>(ps, __builtin_amdgcn_readfirstlane(pid[r]), g * 2u * S::kTile));
+            const int slot = static_cast<int>((w >> kUnitTailShift) & 15u);
+            if (w & kUnitToken) {
+                append_in_place<D, BF16>(ring[r], token, page, slot, koff, voff, lane);
+                token_held = false;
+            } else {  // `token` holds a later row's
+                TokenV<D, BF16> late;
+                load_token_v<D, BF16>(late, a, b, g, lane);
+                append_in_place<D, BF16>(ring[r], late, page, slot, koff, voff, lane);
+            }
+        }
+    };
+    auto compute = [&](int r) __attribute__((always_inline)) {
+        const unsigned w = __builtin_amdgcn_readfirstlane(word[r]);
+        if (w & kUnitNone) return;
+        bad |= (w & kUnitBad) != 0;
+        const int tail = static_cast<int>((w >> kUnitTailShift) & 15u);  // last valid slot
+        compute_page<D, BF16>(st, ring[r], tail + 1, a.scale_log2, qg);
+        if (w & kUnitLast) {
+            const int seg = static_cast<int>(w & kUnitRowMask) * heads + static_cast<int>((w >> kUnitGroupShift) & 15u);
+            const bool seg_last = (w & kUnitSegLast) != 0;
+            if (seg_last && !seg_first) ends.first = seg;
+            if (!seg_last) {
+                ends.last = seg;
+                ends.last_starts = seg_first;
+            }
+            finish_piece<D, BF16, FUSED>(a, st, w, seg_first && seg_last, bad, worker, heads, w_in, lane);
+        }
+    };
+
+    UnitPos at = unit_pos(s_pref, a.batch, heads, u0, lane);
+    UnitChunk nxt = load_units<kChunk>(a, s_pref, heads, at, u1 - u0, true, lane);
+    // steps left: every unit is issued once and computed R - 1 steps later
+    for (int64_t left = u1 - u0 + (R - 1); left > 0; left -= kChunk) {
+        const UnitChunk cur = nxt;
+        const int steps = __builtin_amdgcn_readfirstlane(static_cast<int>(left < kChunk ? left : kChunk));
+        nxt = load_units<kChunk>(a, s_pref, heads, at, left - (R - 1) - kChunk, false, lane);
+        for (int j = 0; j < steps; j += R) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                begin((r + 1) % R);
+                issue(r, cur, j + r);
+                compute((r + 1) % R);
+            }
+        }
+    }
+    return ends;
 }
 
 // ---------------------------------------------------------------------------
@@ -734,6 +1006,75 @@ __device__ __forceinline__ void compute_page_valu(ValuState<D>& st, PageRegs<D, 
     __asm__ volatile("" ::: "memory");  // the next page's weight writes stay after these reads
 }
 
+// Fused append, vector-ALU form: the piece holding a row's last
+// page first writes the row's new token, k_new / v_new row b for this wave's
+// KV head, into that page at slot (L - 1) % 16, then orders those stores before
+// its own loads of the page (the same wave is the only reader of that page's
+// tiles for this KV head in the launch).  Rows with L <= 0 or an invalid L, and
+// tail entries that name no page (or a staging slot), write nothing.
+template <int D, bool BF16, bool TIERED>
+__device__ __forceinline__ void append_new_token(const DecodeArgs& a, const PageSrc& ps, const int32_t* row,
+                                                 const Piece& pc, int nb, int seq_len, int lane) {
+    using S = Shape<D, BF16>;
+    if (!a.k_new || pc.p1 != nb || seq_len <= 0 || a.seq_lens[pc.b] != seq_len) return;
+    unsigned id = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(row[nb - 1]));
+    const char* base = ps.hot;
+    int64_t stride = ps.hot_stride;
+    unsigned n = ps.num_hot;
+    if constexpr (TIERED) {
+        const unsigned tag = id >> 29;  // 0 hot, 2 cold; a staged slot is a copy, not the page
+        id &= static_cast<unsigned>(kPageIdMask);
+        if (tag == 2) {
+            base = ps.cold;
+            stride = ps.cold_stride;
+            n = ps.num_cold;
+        } else if (tag != 0) {
+            n = 0;
+        }
+    }
+    if (id >= n) return;
+    char* lh = const_cast<char*>(base) + static_cast<int64_t>(id) * stride;
+    const int slot = (seq_len - 1) % kPageTokens;
+    const int64_t src = (static_cast<int64_t>(pc.b) * a.num_kv_heads + pc.g) * D * S::kElt;
+    const char* ks = static_cast<const char*>(a.k_new) + src;
+    const char* vs = static_cast<const char*>(a.v_new) + src;
+    constexpr int x = 16 / S::kElt;  // elements per 16-byte group of the K tile
+    if (lane < D / x)
+        *reinterpret_cast<u32x4*>(lh + (static_cast<int64_t>(lane) * kPageTokens + slot) * 16) =
+            *reinterpret_cast<const u32x4*>(ks + 16 * lane);
+    for (int d = lane; d < D; d += kWave) {
+        char* vd = lh + S::kTile + (static_cast<int64_t>(d) * kPageTokens + slot) * S::kElt;
+        if constexpr (BF16)
+            *reinterpret_cast<unsigned short*>(vd) = reinterpret_cast<const unsigned short*>(vs)[d];
+        else
+            *reinterpret_cast<unsigned*>(vd) = reinterpret_cast<const unsigned*>(vs)[d];
+    }
+    // Other lanes of this wave read these bytes back with the page's loads.  A
+    // workgroup-scope release/acquire orders that in the memory model; waiting
+    // for the stores to be acknowledged makes the order independent of how the
+    // L1 treats the nontemporal loads (once per row's tail page: negligible).
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+__device__ __forceinline__ int load_ids(const int32_t* __restrict__ row, int first, int end,
+                                        int lane) {
+    const int i = first + lane;
+    return i < end ? row[i] : -1;
+}
+
+template <int D, bool TIERED>
+__device__ __forceinline__ void load_page_id(PageRegs<D, true>& r, const PageSrc& ps, int pid, bool& bad,
+                                             unsigned koff, unsigned voff) {
+    const PageAddr page = page_addr<TIERED>(ps, pid, 0);
+    const __amdgpu_buffer_rsrc_t rs = page_rsrc<D, true>(page);
+    load_page_k<D, true>(r, rs, koff);
+    load_page_v<D, true>(r, rs, voff);
+    bad |= !page.ok;
+}
+
+// Pages [p0, p1) of row b, KV head g, into the partial's slot or the output.
 template <int D, int R, bool TIERED>
 __device__ void run_piece_valu(const DecodeArgs& a, const Piece& pc, int nb, int seq_len, bool row_invalid,
                                int lane, ValuLds<D>& sm) {
@@ -798,7 +1139,7 @@ __device__ void run_piece_valu(const DecodeArgs& a, const Piece& pc, int nb, int
     PageRegs<D, true> buf[R];
 #pragma unroll
     for (int r = 0; r < R - 1; ++r)
-        if (pc.p0 + r < pc.p1) load_page<D, true, TIERED>(buf[r], ps, pid_at(pc.p0 + r), bad, koff, voff);
+        if (pc.p0 + r < pc.p1) load_page_id<D, TIERED>(buf[r], ps, pid_at(pc.p0 + r), bad, koff, voff);
     for (int i = pc.p0; i < pc.p1; i += R) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -806,7 +1147,7 @@ __device__ void run_piece_valu(const DecodeArgs& a, const Piece& pc, int nb, int
             if (ip < pc.p1) {
                 const int ahead = ip + R - 1;
                 if (ahead < pc.p1)
-                    load_page<D, true, TIERED>(buf[(r + R - 1) % R], ps, pid_at(ahead), bad, koff, voff);
+                    load_page_id<D, TIERED>(buf[(r + R - 1) % R], ps, pid_at(ahead), bad, koff, voff);
                 compute_page_valu<D>(st, buf[r], ip == nb - 1 ? tail_valid : kPageTokens, a.scale_log2,
                                      lane, sm);
             }
@@ -871,62 +1212,93 @@ __device__ void run_piece_valu(const DecodeArgs& a, const Piece& pc, int nb, int
     }
 }
 
-// Register budget of the split kernel: with HCK_SPLIT_WAVES_PER_EU = n the
-// compiler keeps it within 512 / n registers so that n waves fit per SIMD.
-#ifndef HCK_SPLIT_WAVES_PER_EU
-#define HCK_SPLIT_WAVES_PER_EU 1
-#endif
+// Register budget of the split kernel: 512 / n registers, so that n waves fit a
+// SIMD.  With 256 the shapes below keep everything in VGPRs; with 512 the
+// compiler holds the accumulators in AGPRs and moves all of them in and out on
+// every page.  The float32 128-dim shape and the 128-dim fused forms need more
+// than 256.
+template <int D, bool BF16, bool FUSED>
+constexpr int split_waves_per_eu() {
+    return D == 128 && (!BF16 || FUSED) ? 1 : 2;
+}
 
-template <int D, bool BF16, int R, bool TIERED, bool VALU>
-__global__ __launch_bounds__(kSplitBlockThreads)
-__attribute__((amdgpu_waves_per_eu(HCK_SPLIT_WAVES_PER_EU))) void decode_split_kernel(DecodeArgs a) {
-    extern __shared__ int32_t s_pref[];
+// What a wave of the split works on: its worker, its KV head within the
+// worker's head group and its units [u0, u1).
+struct WaveWork {
+    int wave, worker, w_in, heads, lane;
+    int64_t total, u0, u1;
+};
+
+// The row prefix into LDS (and by the first block to the workspace, where the
+// combine reads it), then this wave's share; false for waves past the last.
+__device__ __forceinline__ bool wave_work(const DecodeArgs& a, int32_t* s_pref, WaveWork& w) {
     block_prefix_pages<kSplitBlockThreads>(a.seq_lens, a.batch, a.pt_stride, s_pref);
     __syncthreads();
-    if (blockIdx.x == 0)  // the combine reads the row prefix instead of rescanning the lengths
+    if (blockIdx.x == 0)
         for (int b = threadIdx.x; b <= a.batch; b += kSplitBlockThreads) a.row_pref[b] = s_pref[b];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * kSplitBlockWaves + threadIdx.x / kWave);
-    if (wave >= a.waves) return;
-    // the worker this wave belongs to, and its KV head within the worker's head group
+    w.lane = threadIdx.x & (kWave - 1);
+    w.wave = __builtin_amdgcn_readfirstlane(blockIdx.x * kSplitBlockWaves + threadIdx.x / kWave);
+    if (w.wave >= a.waves) return false;
     const int gw = a.group_waves;
-    const int heads = a.num_kv_heads / gw;
-    const int worker = wave / gw, w_in = wave % gw;
-    // rows with no pages get no pieces: write them here (0 for L = 0, NaN for L < 0)
-    for (int seg = wave; seg < a.batch * a.num_kv_heads; seg += a.waves) {
+    w.heads = a.num_kv_heads / gw;
+    w.worker = w.wave / gw;
+    w.w_in = w.wave % gw;
+    w.total = static_cast<int64_t>(lds_uniform(s_pref + a.batch)) * w.heads;
+    wave_units(w.total, w.worker, a.waves / gw, w.u0, w.u1);
+    return true;
+}
+
+// Rows with no pages get no pieces: their output is written here (0 for L = 0,
+// NaN for L < 0), after the wave's own units.
+template <int D, bool BF16>
+__device__ __forceinline__ void fill_empty_rows(const DecodeArgs& a, const int32_t* s_pref, const WaveWork& w) {
+    for (int seg = w.wave; seg < a.batch * a.num_kv_heads; seg += a.waves) {
         const int b = seg / a.num_kv_heads;
-        const int32_t len = a.seq_lens[b];
-        if (len <= 0)
-            fill_segment<D, BF16>(a, b, seg % a.num_kv_heads, len == 0 ? 0.f : __builtin_nanf(""), lane);
+        if (lds_uniform(s_pref + b) == lds_uniform(s_pref + b + 1))
+            fill_segment<D, BF16>(a, b, seg % a.num_kv_heads, a.seq_lens[b] == 0 ? 0.f : __builtin_nanf(""), w.lane);
     }
-    const int64_t total = static_cast<int64_t>(lds_uniform(s_pref + a.batch)) * heads;
-    int64_t u, u1;
-    wave_units(total, worker, a.waves / gw, u, u1);
-    // the segment (row, head group) whose first piece this worker holds and
-    // whose other pieces belong to later workers: the combine merges it
+}
+
+template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND>
+__global__ __launch_bounds__(kSplitBlockThreads)
+__attribute__((amdgpu_waves_per_eu(split_waves_per_eu<D, BF16, FUSED>()))) void decode_split_kernel(DecodeArgs a) {
+    extern __shared__ int32_t s_pref[];
+    WaveWork w;
+    if (!wave_work(a, s_pref, w)) return;
+    const SplitEnds ends =
+        run_units<D, BF16, R, TIERED, FUSED, APPEND>(a, s_pref, w.u0, w.u1, w.worker, w.heads, w.w_in, w.lane);
+    if constexpr (FUSED)
+        merge_ends<D, BF16>(a, s_pref, ends, w.heads, w.w_in, w.total, w.lane);
+    else if (w.w_in == 0 && w.lane == 0)
+        a.split_segs[w.worker] = ends.last_starts ? ends.last : -1;
+    fill_empty_rows<D, BF16>(a, s_pref, w);
+}
+
+// The vector-ALU form walks its range piece by piece.
+template <int D, int R, bool TIERED>
+__global__ __launch_bounds__(kSplitBlockThreads) void decode_split_valu_kernel(DecodeArgs a) {
+    extern __shared__ int32_t s_pref[];
+    __shared__ ValuLds<D> s_valu[kSplitBlockWaves];
+    WaveWork w;
+    if (!wave_work(a, s_pref, w)) return;
     int32_t split_seg = -1;
-    while (u < u1) {
-        Piece pc = piece_at<true>(s_pref, a.batch, heads, worker, u, u1);
+    int64_t u = w.u0;
+    while (u < w.u1) {
+        Piece pc = piece_at<true>(s_pref, a.batch, w.heads, w.worker, u, w.u1);
         if (pc.p1 <= pc.p0) break;  // cannot happen for a consistent prefix; never spin
         const int nb = lds_uniform(s_pref + pc.b + 1) - lds_uniform(s_pref + pc.b);
         const int32_t len = a.seq_lens[pc.b];
         const int seq_len = len < kPageTokens * nb ? len : kPageTokens * nb;
         const bool row_invalid = static_cast<int64_t>(len) > kPageTokens * a.pt_stride;
-        if (pc.p0 == 0 && pc.p1 < nb) split_seg = pc.b * heads + pc.g;
-        const int64_t seg_first = static_cast<int64_t>(lds_uniform(s_pref + pc.b)) * heads +
-                                  static_cast<int64_t>(pc.g) * nb;
+        if (pc.p0 == 0 && pc.p1 < nb) split_seg = pc.b * w.heads + pc.g;
         const int span = pc.p1 - pc.p0;
-        pc.g = pc.g * gw + w_in;
-        pc.slot = pc.slot * gw + w_in;
-        if constexpr (VALU) {
-            __shared__ ValuLds<D> s_valu[kSplitBlockWaves];
-            run_piece_valu<D, R, TIERED>(a, pc, nb, seq_len, row_invalid, lane, s_valu[threadIdx.x / kWave]);
-        } else {
-            run_piece<D, BF16, R, TIERED>(a, pc, nb, seq_len, row_invalid, lane, seg_first, total);
-        }
+        pc.g = pc.g * a.group_waves + w.w_in;
+        pc.slot = pc.slot * a.group_waves + w.w_in;
+        run_piece_valu<D, R, TIERED>(a, pc, nb, seq_len, row_invalid, w.lane, s_valu[threadIdx.x / kWave]);
         u += span;
     }
-    if (!a.fused && w_in == 0 && lane == 0) a.split_segs[worker] = split_seg;
+    if (w.w_in == 0 && w.lane == 0) a.split_segs[w.worker] = split_seg;
+    fill_empty_rows<D, true>(a, s_pref, w);
 }
 
 // Merge the partials of one (b, g) for one query head and write its output row.
@@ -1051,7 +1423,7 @@ __global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArg
         const float nan = __builtin_nanf("");
         res = f32x4{nan, nan, nan, nan};
     } else {
-        res = acc / den;
+        res = BF16 ? acc * (1.0f / den) : acc / den;
     }
     if (grp == 0) {
         const int64_t orow =
@@ -1074,23 +1446,40 @@ constexpr int ring_depth() {
     return BF16 ? (D == 128 ? HCK_RING_BF16_D128 : 5) : (D == 128 ? 2 : 3);
 }
 
-template <int D, bool BF16, bool VALU>
-const void* split_kernel_ptr(bool tiered) {
+template <int D, bool BF16, bool TIERED>
+const void* split_kernel_ptr(bool fused, bool append) {
     constexpr int R = ring_depth<D, BF16>();
-    return tiered ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, true, VALU>)
-                  : reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, false, VALU>);
+    if (fused)
+        return append ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, true, true>)
+                      : reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, true, false>);
+    return append ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, false, true>)
+                  : reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, false, false>);
+}
+
+template <int D, bool BF16>
+const void* split_kernel_ptr(bool tiered, bool fused, bool append) {
+    return tiered ? split_kernel_ptr<D, BF16, true>(fused, append) : split_kernel_ptr<D, BF16, false>(fused, append);
+}
+
+template <int D>
+const void* valu_kernel_ptr(bool tiered) {
+    constexpr int R = ring_depth<D, true>();
+    return tiered ? reinterpret_cast<const void*>(&decode_split_valu_kernel<D, R, true>)
+                  : reinterpret_cast<const void*>(&decode_split_valu_kernel<D, R, false>);
 }
 
 // The vector-ALU variant exists for bf16 only.
-const void* pick_split(int head_dim, int dtype, bool tiered, bool valu) {
+const void* pick_split(int head_dim, int dtype, bool tiered, bool valu, bool fused, bool append) {
+    if (valu) {
+        if (dtype != kDtypeBf16) return nullptr;
+        return head_dim == 128 ? valu_kernel_ptr<128>(tiered) : head_dim == 64 ? valu_kernel_ptr<64>(tiered) : nullptr;
+    }
     if (dtype == kDtypeBf16) {
-        if (head_dim == 128)
-            return valu ? split_kernel_ptr<128, true, true>(tiered) : split_kernel_ptr<128, true, false>(tiered);
-        if (head_dim == 64)
-            return valu ? split_kernel_ptr<64, true, true>(tiered) : split_kernel_ptr<64, true, false>(tiered);
-    } else if (!valu) {
-        if (head_dim == 128) return split_kernel_ptr<128, false, false>(tiered);
-        if (head_dim == 64) return split_kernel_ptr<64, false, false>(tiered);
+        if (head_dim == 128) return split_kernel_ptr<128, true>(tiered, fused, append);
+        if (head_dim == 64) return split_kernel_ptr<64, true>(tiered, fused, append);
+    } else {
+        if (head_dim == 128) return split_kernel_ptr<128, false>(tiered, fused, append);
+        if (head_dim == 64) return split_kernel_ptr<64, false>(tiered, fused, append);
     }
     return nullptr;
 }
@@ -1123,7 +1512,7 @@ hipError_t launch_decode_split(const DecodeArgs& a, int head_dim, int dtype, hip
     if (a.group_waves < 1 || kSplitBlockWaves % a.group_waves || a.num_kv_heads % a.group_waves ||
         a.waves % a.group_waves)
         return hipErrorInvalidValue;
-    const void* k = pick_split(head_dim, dtype, a.tiered != 0, a.valu != 0);
+    const void* k = pick_split(head_dim, dtype, a.tiered != 0, a.valu != 0, a.fused != 0, a.k_new != nullptr);
     if (!k || a.waves <= 0) return hipErrorInvalidValue;
     const int blocks = (a.waves + kSplitBlockWaves - 1) / kSplitBlockWaves;
     void* args[] = {const_cast<DecodeArgs*>(&a)};
@@ -1154,7 +1543,7 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
 }
 
 int decode_split_blocks_per_cu(int head_dim, int dtype, int batch) {
-    const void* k = pick_split(head_dim, dtype, false, false);
+    const void* k = pick_split(head_dim, dtype, false, false, false, false);
     if (!k) return 0;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kSplitBlockThreads, prefix_lds_bytes(batch)) !=

@@ -72,8 +72,19 @@ __device__ __forceinline__ int32_t lds_uniform(const int32_t* p) {
 // Units are (row, head group, page) triples ordered by row, then head group,
 // then page; worker k of `workers` owns units
 // [floor(k T / workers), floor((k + 1) T / workers)).
+// One 32-bit division gives both where the numbers fit (k T / N = k (T / N) +
+// k (T mod N) / N): 64-bit divisions are about 100 instructions each, in front
+// of a wave's first load.
 __device__ __forceinline__ void wave_units(int64_t total_units, int worker, int workers, int64_t& u0,
                                            int64_t& u1) {
+    if ((total_units >> 32) == 0 && workers <= 0xFFFF) {
+        const unsigned n = static_cast<unsigned>(workers), k = static_cast<unsigned>(worker);
+        const unsigned q = static_cast<unsigned>(total_units) / n;
+        const unsigned r = static_cast<unsigned>(total_units) - q * n;
+        u0 = k * q + k * r / n;
+        u1 = (k + 1) * q + (k + 1) * r / n;
+        return;
+    }
     u0 = static_cast<int64_t>(worker) * total_units / workers;
     u1 = static_cast<int64_t>(worker + 1) * total_units / workers;
 }

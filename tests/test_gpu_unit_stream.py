@@ -1,0 +1,74 @@
+"""The split's unit stream at its edges (GPU): a wave walks consecutive pages of
+many rows, 60 to 64 of them per chunk, with its ring running on from row to row."""
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from helpers import Case, build_gpu, rowwise_check, to_device, to_host, tolerance_check
+
+pytestmark = pytest.mark.gpu
+
+# runs of empty rows, rows of one to three pages (shorter than the ring), rows
+# that end on a chunk's last unit and one past it, and one of several chunks
+LENS = [1, 0, 0, 0, 16, 17, 33, 48, 5, 0, 60 * 16, 1, 63 * 16, 64 * 16 + 1, 2, 18, 0, 200 * 16 - 7, 31, 32, 0, 0]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch.device("cuda", 0)
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("dtype,D,hq,hkv,waves", [
+    ("bf16", 128, 16, 4, 4), ("bf16", 128, 16, 4, 768), ("bf16", 64, 16, 16, 8), ("bf16", 64, 6, 2, 1),
+    ("f32", 128, 8, 8, 12), ("f32", 64, 4, 1, 3)])
+def test_rows_of_every_length_against_the_oracle(dev, dtype, D, hq, hkv, waves, fused):
+    """One to four head groups per row and workers of one and four waves; with
+    few waves each walks several chunks."""
+    case = Case(1, hq, hkv, D, dtype, LENS, seed=41)
+    pool = build_gpu(case, dev, poison=True)
+    pool.set_waves(waves)
+    pool.set_combine(fused)
+    got = to_host(pool.decode(0, to_device(case.q, dtype, dev), torch.tensor(LENS, dtype=torch.int32, device=dev)))
+    pool.close()
+    rowwise_check(got, case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("dtype,D,hq,hkv,waves", [
+    ("bf16", 128, 16, 4, 4), ("bf16", 64, 16, 16, 8), ("f32", 128, 8, 8, 12), ("f32", 64, 4, 1, 3),
+    ("bf16", 128, 8, 1, 64)])
+def test_append_into_consecutive_short_rows(dev, dtype, D, hq, hkv, waves):
+    """Tail pages one to three units apart: a wave holds one row's new token
+    while it meets the next ones'.  Bitwise equal to a separate append, pages
+    included."""
+    kvs = [synth.session_kv(43, b, L, 0, hkv, D, 1.0, dtype) for b, L in enumerate(LENS)]
+    case = Case(1, hq, hkv, D, dtype, LENS, seed=43)
+    q = to_device(case.q, dtype, dev)
+    sl = torch.tensor(LENS, dtype=torch.int32, device=dev)
+    rows = [b for b, L in enumerate(LENS) if L]
+    new = [np.zeros((len(LENS), hkv, D), kvs[0][0].dtype) for _ in range(2)]
+    for b in rows:
+        for i in range(2):
+            new[i][b] = kvs[b][i][LENS[b] - 1]
+    kn, vn = (to_device(t, dtype, dev) for t in new)
+    outs, hots = [], []
+    for fused_append in (True, False):
+        pool = build_gpu(case, dev, poison=True)
+        pool.set_waves(waves)
+        for b in rows:   # the last token's slot holds NaN until it is appended
+            nan = torch.full((1, hkv, D), float("nan"), dtype=kn.dtype, device=dev)
+            pool.write_tokens(b, 0, LENS[b] - 1, nan, nan)
+        if fused_append:
+            outs.append(pool.decode(0, q, sl, k_new=kn, v_new=vn).clone())
+        else:
+            pool.append_tokens(0, rows, [LENS[b] - 1 for b in rows], kn[rows].contiguous(), vn[rows].contiguous())
+            outs.append(pool.decode(0, q, sl).clone())
+        torch.cuda.synchronize()
+        hots.append(pool.hot.clone())
+        pool.close()
+    assert torch.equal(hots[0], hots[1])
+    assert torch.equal(outs[0], outs[1])
+    tolerance_check(to_host(outs[0]), case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
