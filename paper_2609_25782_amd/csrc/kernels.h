@@ -79,8 +79,10 @@ struct DecodeArgs {
 };
 
 // Events a launch records at its kernel's start and end (the library's
-// profiling); both null for a plain launch.  The timestamps come from the
-// dispatch itself, so they bracket the kernel and nothing else.
+// profiling) or at its end only (a mark for other streams or the host: part of
+// the dispatch, where an event record is a packet of its own that the next
+// kernel waits 5 us for); both null for a plain launch.  The timestamps come
+// from the dispatch itself, so they bracket the kernel and nothing else.
 struct LaunchEvents {
     hipEvent_t start = nullptr;
     hipEvent_t stop = nullptr;
@@ -88,7 +90,7 @@ struct LaunchEvents {
 
 inline hipError_t launch_kernel(const void* k, dim3 grid, dim3 block, void** args, size_t lds,
                                 hipStream_t s, const LaunchEvents& ev) {
-    if (ev.start && ev.stop) return hipExtLaunchKernel(k, grid, block, args, lds, s, ev.start, ev.stop, 0);
+    if (ev.stop) return hipExtLaunchKernel(k, grid, block, args, lds, s, ev.start, ev.stop, 0);
     return hipLaunchKernel(k, grid, block, args, lds, s);
 }
 
@@ -163,19 +165,48 @@ struct CopyEntry {
 // num_layers.  One layer's slices into the staging buffer: layers = 1, src
 // based at that layer.  by_layer walks the copy layer by layer instead of page
 // by page (for copies out of the layer-major hot pool).  max_blocks caps the
-// persistent grid (0: the default).
+// persistent grid (0: the default).  on_host: `entries` is host memory, read by
+// this call and carried in the kernel arguments (at most kCopyInline of them).
+constexpr int kCopyInline = 128;
 hipError_t launch_page_copy(const PoolGeom& src, const PoolGeom& dst, int64_t slice_bytes, int32_t layers,
-                            bool by_layer, const CopyEntry* entries, int32_t n, int32_t* page_table,
+                            bool by_layer, const CopyEntry* entries, bool on_host, int32_t n, int32_t* page_table,
                             int32_t max_blocks, hipStream_t s, const LaunchEvents& ev = {});
 
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t value, hipStream_t s);
+
+// A list in pinned host memory (its device-visible address) into device memory,
+// by a kernel: both buffers hold whole 16-byte words.
+hipError_t launch_upload(const void* host, void* dev, size_t bytes, hipStream_t s);
+
+// row[0 .. n) = host[0 .. n), host in pinned host memory (its device-visible address).
+hipError_t launch_upload_row(const int32_t* host, int32_t* row, int32_t n, hipStream_t s);
+
+// row[0 .. n) = ids[0 .. n), the ids in the kernel arguments.
+constexpr int kRowInline = 512;
+struct RowArgs {
+    int32_t* row;
+    int32_t n;
+    int32_t ids[kRowInline];
+};
+hipError_t launch_write_row(const RowArgs& a, hipStream_t s);
+
+// Page-table rows cleared by one launch, their numbers in the kernel arguments.
+constexpr int kClearRows = 128;
+struct ClearRowsArgs {
+    int32_t* page_table;
+    int64_t stride;
+    int32_t row[kClearRows];
+    int32_t count[kClearRows];  // entries set to -1, from the row's first
+};
+hipError_t launch_clear_rows(const ClearRowsArgs& a, int32_t rows, hipStream_t s, const LaunchEvents& ev = {});
 
 // Streaming read of `bytes` (a multiple of 16) at buf by `blocks` blocks; one
 // XOR word per block to out[0 .. blocks).
 hipError_t launch_read_probe(const void* buf, int64_t bytes, uint32_t* out, int32_t blocks, hipStream_t s);
 
 // page_table[e.pt_index] = e.pt_value for each of n entries with pt_index >= 0
-// (no copies): the second phase of a promotion.
+// (no copies).  Each entry is read once, so the list may stay in pinned host
+// memory.
 hipError_t launch_table_writes(const CopyEntry* entries, int32_t n, int32_t* page_table, hipStream_t s);
 
 struct SynthArgs {

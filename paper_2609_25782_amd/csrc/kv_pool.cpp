@@ -113,7 +113,8 @@ constexpr int32_t kMaxDecodeBatch = hck::kMaxDecodeBatch;
 constexpr int32_t kDecodeWavesPerCu = HCK_DECODE_WAVES_PER_CU;
 
 struct StagingSlot {
-    void* host = nullptr;  // pinned
+    void* host = nullptr;    // pinned
+    void* mapped = nullptr;  // the device's address of `host`
     void* dev = nullptr;
     hipEvent_t done = nullptr;
     bool pending = false;
@@ -278,10 +279,11 @@ struct kv_pool {
         return KV_OK;
     }
 
-    // After a call that freed hot pages enqueued its work on `s`.  Marks of other
-    // streams whose work has finished are dropped; a single shared event would
-    // lose the work of the previous freeing call whenever streams alternate.
-    int note_frees(hipStream_t s) {
+    // The mark of stream `s` (made on first use), to be recorded after the work
+    // of a call that frees hot pages.  Marks of other streams whose work has
+    // finished are dropped; a single shared event would lose the work of the
+    // previous freeing call whenever streams alternate.
+    int free_mark(hipStream_t s, hipEvent_t* out) {
         size_t keep = 0;
         for (size_t i = 0; i < free_marks.size(); ++i) {
             const FreeMark m = free_marks[i];
@@ -292,19 +294,33 @@ struct kv_pool {
             free_marks[keep++] = m;
         }
         free_marks.resize(keep);
-        FreeMark* mine = nullptr;
-        for (FreeMark& m : free_marks)
-            if (m.stream == s) mine = &m;
-        if (!mine) {
-            hipEvent_t ev = nullptr;
-            hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-            if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
-            free_marks.push_back(FreeMark{s, ev});
-            mine = &free_marks.back();
-        }
-        hipError_t e = hipEventRecord(mine->event, s);
+        for (const FreeMark& m : free_marks)
+            if (m.stream == s) {
+                *out = m.event;
+                return KV_OK;
+            }
+        hipEvent_t ev = nullptr;
+        hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
+        free_marks.push_back(FreeMark{s, ev});
+        *out = ev;
+        return KV_OK;
+    }
+
+    int note_frees(hipStream_t s) {
+        hipEvent_t ev;
+        int rc = free_mark(s, &ev);
+        if (rc) return rc;
+        hipError_t e = hipEventRecord(ev, s);
         if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
         return KV_OK;
+    }
+
+    // Whether a launch may record `s`'s events itself: not while it is captured,
+    // where only an event record is a node of the graph.
+    static bool plain_stream(hipStream_t s) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        return hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
     }
 
     int acquire_slot(StagingSlot** out) {
@@ -316,6 +332,14 @@ struct kv_pool {
             s.pending = false;
         }
         *out = &s;
+        return KV_OK;
+    }
+
+    // The slot's lists are in use until the work enqueued on `s` so far is done.
+    int release_slot(StagingSlot* slot, hipStream_t s) {
+        hipError_t e = hipEventRecord(slot->done, s);
+        if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
+        slot->pending = true;
         return KV_OK;
     }
 
@@ -356,43 +380,47 @@ struct kv_pool {
     }
 
     // Enqueue whole-page copies between the pools (in chunks that fit a
-    // staging slot): cold -> hot when to_hot, else hot -> cold.  Entries that
-    // only write the page table (rows cleared on eviction, resident pages
-    // remapped on resume) go to the table-write kernel instead, so the copy
+    // staging slot): cold -> hot when to_hot, else hot -> cold.  `writes` are
+    // page-table entries without a copy (rows cleared on eviction, resident
+    // pages remapped on resume): they go to the table-write kernel, so the copy
     // grid only walks pages that move.
-    int submit_copies(bool to_hot, const std::vector<hck::CopyEntry>& all, hipStream_t s, int kernel_id) {
-        std::vector<hck::CopyEntry> entries, writes;
-        entries.reserve(all.size());
-        for (const hck::CopyEntry& e : all) {
-            if (e.src >= 0)
-                entries.push_back(e);
-            else if (e.pt_index >= 0)
-                writes.push_back(e);
-        }
+    int submit_copies(bool to_hot, const std::vector<hck::CopyEntry>& copies,
+                      const std::vector<hck::CopyEntry>& writes, hipStream_t s, int kernel_id) {
         if (!writes.empty()) {
             int rc = submit_table_writes(writes, s);
             if (rc) return rc;
         }
-        if (cold_host && host_copy == KV_HOST_COPY_DMA) return submit_dma_copies(to_hot, entries, s, kernel_id);
+        if (cold_host && host_copy == KV_HOST_COPY_DMA) return submit_dma_copies(to_hot, copies, s, kernel_id);
         const hck::PoolGeom& src = to_hot ? cold_geom : hot_geom;
         const hck::PoolGeom& dst = to_hot ? hot_geom : cold_geom;
-        for (size_t off = 0; off < entries.size(); off += kStagingEntries) {
-            const int32_t n = static_cast<int32_t>(
-                std::min<size_t>(kStagingEntries, entries.size() - off));
+        if (!copies.empty() && copies.size() <= static_cast<size_t>(hck::kCopyInline)) {
+            const hck::LaunchEvents ev = prof_events();
+            hipError_t e = hck::launch_page_copy(src, dst, slice_bytes, d.num_layers, /*by_layer=*/!to_hot,
+                                                 copies.data(), /*on_host=*/true, static_cast<int32_t>(copies.size()),
+                                                 pt, copy_blocks, s, ev);
+            prof_done(kernel_id, ev, e);
+            return e == hipSuccess ? KV_OK : hip_fail(e, "page copy launch");
+        }
+        for (size_t off = 0; off < copies.size(); off += kStagingEntries) {
+            const int32_t n = static_cast<int32_t>(std::min<size_t>(kStagingEntries, copies.size() - off));
             StagingSlot* slot;
             int rc = acquire_slot(&slot);
             if (rc) return rc;
-            std::memcpy(slot->host, entries.data() + off, n * sizeof(hck::CopyEntry));
-            hipError_t e = hipMemcpyAsync(slot->dev, slot->host, n * sizeof(hck::CopyEntry),
-                                          hipMemcpyHostToDevice, s);
-            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(copy list)");
-            const hck::LaunchEvents ev = prof_events();
+            std::memcpy(slot->host, copies.data() + off, n * sizeof(hck::CopyEntry));
+            hipError_t e = hck::launch_upload(slot->mapped, slot->dev, n * sizeof(hck::CopyEntry), s);
+            if (e != hipSuccess) return hip_fail(e, "copy list upload");
+            hck::LaunchEvents ev = prof_events();
+            const bool own_event = !ev.start && plain_stream(s);
+            if (own_event) ev.stop = slot->done;  // recorded by the copy's own dispatch
             e = hck::launch_page_copy(src, dst, slice_bytes, d.num_layers, /*by_layer=*/!to_hot,
-                                      static_cast<const hck::CopyEntry*>(slot->dev), n, pt, copy_blocks, s, ev);
+                                      static_cast<const hck::CopyEntry*>(slot->dev), /*on_host=*/false, n, pt,
+                                      copy_blocks, s, ev);
             prof_done(kernel_id, ev, e);
             if (e != hipSuccess) return hip_fail(e, "page copy launch");
-            e = hipEventRecord(slot->done, s);
-            if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
+            if (!own_event) {
+                rc = release_slot(slot, s);
+                if (rc) return rc;
+            }
             slot->pending = true;
         }
         return KV_OK;
@@ -452,56 +480,63 @@ struct kv_pool {
             int rc = acquire_slot(&slot);
             if (rc) return rc;
             std::memcpy(slot->host, entries.data() + off, n * sizeof(hck::CopyEntry));
-            hipError_t e = hipMemcpyAsync(slot->dev, slot->host, n * sizeof(hck::CopyEntry),
-                                          hipMemcpyHostToDevice, s);
-            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(table writes)");
-            e = hck::launch_table_writes(static_cast<const hck::CopyEntry*>(slot->dev), n, pt, s);
+            hipError_t e = hck::launch_table_writes(static_cast<const hck::CopyEntry*>(slot->mapped), n, pt, s);
             if (e != hipSuccess) return hip_fail(e, "table write launch");
-            e = hipEventRecord(slot->done, s);
-            if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
-            slot->pending = true;
+            rc = release_slot(slot, s);
+            if (rc) return rc;
         }
         return KV_OK;
     }
 
-    // Write `n` page ids into page-table row `sid` (entries 0..n-1).
-    int submit_row(int32_t sid, const int32_t* vals, int32_t n, hipStream_t s) {
-        if (n <= 0) return KV_OK;
-        StagingSlot* slot;
-        int rc = acquire_slot(&slot);
-        if (rc) return rc;
-        std::memcpy(slot->host, vals, n * sizeof(int32_t));
-        hipError_t e = hipMemcpyAsync(pt + static_cast<int64_t>(sid) * d.max_pages_per_session,
-                                      slot->host, n * sizeof(int32_t), hipMemcpyHostToDevice, s);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(page-table row)");
-        e = hipEventRecord(slot->done, s);
-        if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
-        slot->pending = true;
-        return KV_OK;
-    }
-
-    int clear_row(int32_t sid, int32_t n, hipStream_t s) {
-        if (n <= 0) return KV_OK;
-        hipError_t e =
-            hck::launch_fill_i32(pt + static_cast<int64_t>(sid) * d.max_pages_per_session, n, -1, s);
-        if (e != hipSuccess) return hip_fail(e, "page-table clear");
-        return KV_OK;
+    // Clear the sessions' rows (ids and counts in the kernel arguments: no list,
+    // no staging slot) and mark the stream: their hot pages are free after it.
+    int clear_rows_and_free(const std::vector<int32_t>& sids, hipStream_t s) {
+        hck::LaunchEvents mark;  // recorded by the last launch
+        const bool own_event = plain_stream(s);
+        if (own_event) {
+            int rc = free_mark(s, &mark.stop);
+            if (rc) return rc;
+        }
+        for (size_t off = 0; off < sids.size(); off += hck::kClearRows) {
+            hck::ClearRowsArgs a;
+            a.page_table = pt;
+            a.stride = d.max_pages_per_session;
+            const int32_t n = static_cast<int32_t>(std::min<size_t>(hck::kClearRows, sids.size() - off));
+            for (int32_t i = 0; i < n; ++i) {
+                a.row[i] = sids[off + i];
+                a.count[i] = static_cast<int32_t>(sessions[sids[off + i]].hot.size());
+            }
+            const bool last = off + n == sids.size();
+            hipError_t e = hck::launch_clear_rows(a, n, s, last ? mark : hck::LaunchEvents{});
+            if (e != hipSuccess) return hip_fail(e, "page-table clear");
+        }
+        return own_event ? KV_OK : note_frees(s);
     }
 
     // Write `n` page ids into page-table row `sid` starting at entry `first`.
     int submit_row_at(int32_t sid, int32_t first, const int32_t* vals, int32_t n, hipStream_t s) {
-        if (n <= 0) return KV_OK;
-        StagingSlot* slot;
-        int rc = acquire_slot(&slot);
-        if (rc) return rc;
-        std::memcpy(slot->host, vals, n * sizeof(int32_t));
-        hipError_t e = hipMemcpyAsync(
-            pt + static_cast<int64_t>(sid) * d.max_pages_per_session + first, slot->host,
-            n * sizeof(int32_t), hipMemcpyHostToDevice, s);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(page-table row)");
-        e = hipEventRecord(slot->done, s);
-        if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
-        slot->pending = true;
+        if (n > 0 && n <= hck::kRowInline) {
+            hck::RowArgs a;
+            a.row = pt + static_cast<int64_t>(sid) * d.max_pages_per_session + first;
+            a.n = n;
+            std::memcpy(a.ids, vals, n * sizeof(int32_t));
+            hipError_t e = hck::launch_write_row(a, s);
+            return e == hipSuccess ? KV_OK : hip_fail(e, "page-table row");
+        }
+        constexpr int32_t kIds = static_cast<int32_t>(kStagingBytes / sizeof(int32_t));
+        for (int32_t off = 0; off < n; off += kIds) {
+            const int32_t m = std::min(kIds, n - off);
+            StagingSlot* slot;
+            int rc = acquire_slot(&slot);
+            if (rc) return rc;
+            std::memcpy(slot->host, vals + off, m * sizeof(int32_t));
+            hipError_t e = hck::launch_upload_row(static_cast<const int32_t*>(slot->mapped),
+                                                  pt + static_cast<int64_t>(sid) * d.max_pages_per_session + first + off,
+                                                  m, s);
+            if (e != hipSuccess) return hip_fail(e, "page-table row");
+            rc = release_slot(slot, s);
+            if (rc) return rc;
+        }
         return KV_OK;
     }
 
@@ -596,17 +631,17 @@ struct kv_pool {
     // launch that reuses their hot pages on the same stream.
     int submit_victims(const Alloc& a, hipStream_t s) {
         if (a.victims.empty()) return KV_OK;
-        std::vector<hck::CopyEntry> entries;
-        entries.reserve(a.victims.size());
-        size_t k = 0;
+        std::vector<hck::CopyEntry> copies, writes;
+        copies.reserve(a.victim_cold.size());
         for (const Victim& v : a.victims) {
             const Session& ss = sessions[v.sid];
-            const bool copy = ss.cold[v.page] < 0;
-            entries.push_back(hck::CopyEntry{copy ? ss.hot[v.page] : -1, copy ? a.victim_cold[k] : -1,
-                                             v.sid * d.max_pages_per_session + v.page, -1});
-            k += copy;
+            const int32_t at = v.sid * d.max_pages_per_session + v.page;
+            if (ss.cold[v.page] < 0)
+                copies.push_back(hck::CopyEntry{ss.hot[v.page], a.victim_cold[copies.size()], at, -1});
+            else
+                writes.push_back(hck::CopyEntry{-1, -1, at, -1});
         }
-        int rc = submit_copies(false, entries, s, KV_KERNEL_EVICT_COPY);
+        int rc = submit_copies(false, copies, writes, s, KV_KERNEL_EVICT_COPY);
         if (!rc) rc = note_frees(s);
         return rc;
     }
@@ -715,6 +750,7 @@ int kv_pool_create(const kv_pool_desc* desc, void* hot_base, size_t hot_bytes, v
         }
         for (auto& s : p->ring) {
             if (hipHostMalloc(&s.host, kStagingBytes, hipHostMallocDefault) != hipSuccess ||
+                hipHostGetDevicePointer(&s.mapped, s.host, 0) != hipSuccess ||
                 hipMalloc(&s.dev, kStagingBytes) != hipSuccess ||
                 hipEventCreateWithFlags(&s.done, hipEventDisableTiming) != hipSuccess) {
                 delete p;
@@ -938,8 +974,7 @@ int kv_session_destroy(kv_pool* pool, int32_t sid, kv_stream_t stream) {
     if (!pool->meta && kv_pool::has_row_entries(*s)) {
         DeviceGuard g(pool->d.device);
         hipStream_t st = pool->strm(stream);
-        int rc = pool->clear_row(sid, static_cast<int32_t>(s->hot.size()), st);
-        if (!rc) rc = pool->note_frees(st);
+        int rc = pool->clear_rows_and_free({sid}, st);
         if (rc) return rc;
     }
     for (int32_t p : s->hot)
@@ -1009,9 +1044,8 @@ int kv_append_tokens(kv_pool* pool, int32_t layer, const int32_t* sids, const in
         }
         a.entries = nullptr;
         if (slot) {
-            hipError_t e = hipMemcpyAsync(slot->dev, slot->host, static_cast<size_t>(n) * sizeof(hck::AppendEntry),
-                                          hipMemcpyHostToDevice, st);
-            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(append list)");
+            hipError_t e = hck::launch_upload(slot->mapped, slot->dev, static_cast<size_t>(n) * sizeof(hck::AppendEntry), st);
+            if (e != hipSuccess) return hip_fail(e, "append list upload");
             a.entries = static_cast<const hck::AppendEntry*>(slot->dev);
         }
         a.hot = pool->hot_geom;
@@ -1026,9 +1060,8 @@ int kv_append_tokens(kv_pool* pool, int32_t layer, const int32_t* sids, const in
         hipError_t e = hck::launch_append_tokens(a, st);
         if (e != hipSuccess) return hip_fail(e, "append_tokens launch");
         if (slot) {
-            e = hipEventRecord(slot->done, st);
-            if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
-            slot->pending = true;
+            int rc = pool->release_slot(slot, st);
+            if (rc) return rc;
         }
     }
     for (int32_t i = 0; i < n; ++i) {      // a written hot page loses its cold copy
@@ -1229,7 +1262,7 @@ int kv_promote_pages(kv_pool* pool, int32_t n, kv_stream_t stream, int32_t* prom
         }
         rc = pool->order_after_frees(st);
         if (!rc) rc = pool->submit_victims(a, st);
-        if (!rc) rc = pool->submit_copies(true, copies, st, KV_KERNEL_PAGE_COPY);
+        if (!rc) rc = pool->submit_copies(true, copies, {}, st, KV_KERNEL_PAGE_COPY);
         if (!rc) rc = pool->submit_table_writes(writes, st);
         if (rc) return rc;
     }
@@ -1274,20 +1307,16 @@ int kv_evict_sessions(kv_pool* pool, const int32_t* sids, int32_t n, kv_stream_t
     if (!pool->meta) {
         DeviceGuard g(pool->d.device);
         hipStream_t st = pool->strm(stream);
+        // only the dirty pages make a list; the rows are cleared by range
         std::vector<hck::CopyEntry> entries;
-        size_t k = 0;
+        entries.reserve(dst.size());
         for (int32_t sid : ids) {
             const Session& s = pool->sessions[sid];
-            const int32_t row = sid * pool->d.max_pages_per_session;
-            for (size_t i = 0; i < s.hot.size(); ++i) {
-                const bool copy = s.cold[i] < 0;
-                entries.push_back(hck::CopyEntry{copy ? s.hot[i] : -1, copy ? dst[k] : -1,
-                                                 row + static_cast<int32_t>(i), -1});
-                k += copy;
-            }
+            for (size_t i = 0; i < s.hot.size(); ++i)
+                if (s.cold[i] < 0) entries.push_back(hck::CopyEntry{s.hot[i], dst[entries.size()], -1, -1});
         }
-        int rc = pool->submit_copies(false, entries, st, KV_KERNEL_EVICT_COPY);
-        if (!rc) rc = pool->note_frees(st);
+        int rc = pool->submit_copies(false, entries, {}, st, KV_KERNEL_EVICT_COPY);
+        if (!rc) rc = pool->clear_rows_and_free(ids, st);
         if (rc) return rc;
     }
     size_t k = 0;
@@ -1343,27 +1372,26 @@ int kv_resume_sessions(kv_pool* pool, const int32_t* sids, int32_t n, kv_stream_
     if (!pool->meta) {
         DeviceGuard g(pool->d.device);
         hipStream_t st = pool->strm(stream);
-        std::vector<hck::CopyEntry> entries;
-        size_t k = 0;
+        std::vector<hck::CopyEntry> copies, writes;
+        copies.reserve(a.pages.size());
         for (int32_t sid : ids) {
             const Session& s = pool->sessions[sid];
             const int32_t row = sid * pool->d.max_pages_per_session;
             for (size_t i = 0; i < s.hot.size(); ++i) {
-                if (s.hot[i] < 0 && k < a.pages.size()) {
-                    entries.push_back(hck::CopyEntry{s.cold[i], a.pages[k], row + static_cast<int32_t>(i),
-                                                     a.pages[k]});
-                    ++k;
-                } else if (s.hot[i] < 0) {
-                    entries.push_back(hck::CopyEntry{-1, -1, row + static_cast<int32_t>(i),
-                                                     s.cold[i] | KV_PAGE_COLD});
+                const int32_t at = row + static_cast<int32_t>(i);
+                if (s.hot[i] >= 0) {
+                    writes.push_back(hck::CopyEntry{-1, -1, at, s.hot[i]});
+                } else if (copies.size() < a.pages.size()) {
+                    const int32_t p = a.pages[copies.size()];
+                    copies.push_back(hck::CopyEntry{s.cold[i], p, at, p});
                 } else {
-                    entries.push_back(hck::CopyEntry{-1, -1, row + static_cast<int32_t>(i), s.hot[i]});
+                    writes.push_back(hck::CopyEntry{-1, -1, at, s.cold[i] | KV_PAGE_COLD});
                 }
             }
         }
         rc = pool->order_after_frees(st);
         if (!rc) rc = pool->submit_victims(a, st);
-        if (!rc) rc = pool->submit_copies(true, entries, st, KV_KERNEL_PAGE_COPY);
+        if (!rc) rc = pool->submit_copies(true, copies, writes, st, KV_KERNEL_PAGE_COPY);
         if (rc) return rc;
     }
     pool->commit_victims(a);
@@ -1732,12 +1760,11 @@ int paged_decode_stage(kv_pool* pool, const int32_t* sids, int32_t n, int32_t* t
         int rc = pool->acquire_slot(&slot);
         if (rc) return rc;
         std::memcpy(slot->host, rows.data() + static_cast<size_t>(b0) * stride, m * row_bytes);
-        hipError_t e = hipMemcpyAsync(table + static_cast<size_t>(b0) * stride, slot->host, m * row_bytes,
-                                      hipMemcpyHostToDevice, st);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(batch table)");
-        e = hipEventRecord(slot->done, st);
-        if (e != hipSuccess) return hip_fail(e, "hipEventRecord(staging)");
-        slot->pending = true;
+        hipError_t e = hck::launch_upload_row(static_cast<const int32_t*>(slot->mapped),
+                                              table + static_cast<size_t>(b0) * stride, m * stride, st);
+        if (e != hipSuccess) return hip_fail(e, "batch table upload");
+        rc = pool->release_slot(slot, st);
+        if (rc) return rc;
     }
     if (!plan.empty()) {
         for (size_t k = 0; k < plan.size(); ++k)
@@ -1773,7 +1800,7 @@ int paged_decode_prefetch(kv_pool* pool, int32_t layer, kv_stream_t copy_stream)
                             pool->slice_bytes, 0};
     const hck::LaunchEvents ev = pool->prof_events();
     e = hck::launch_page_copy(src, dst, pool->slice_bytes, 1, false, pool->plan_dev,
-                              static_cast<int32_t>(pool->plan.size()), nullptr, pool->copy_blocks, cs, ev);
+                              /*on_host=*/false, static_cast<int32_t>(pool->plan.size()), nullptr, pool->copy_blocks, cs, ev);
     pool->prof_done(KV_KERNEL_PREFETCH_COPY, ev, e);
     if (e != hipSuccess) return hip_fail(e, "prefetch launch");
     e = hipEventRecord(pool->half_ready[half], cs);

@@ -64,10 +64,26 @@ __device__ __forceinline__ char* entry_slice(const PoolGeom& hot, const PoolGeom
 // it at a time, which address translation serves far better than slices
 // spread over the whole pool (reads stall on it; the scattered writes of the
 // other direction are posted and hurt less).
-template <int U>
-__global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(
-    const PoolGeom src, const PoolGeom dst, const CopyEntry* __restrict__ entries, int32_t n,
-    int chunks_per_entry, int chunks_per_slice, int by_layer, int32_t* __restrict__ page_table) {
+// Short lists (kCopyInline entries) travel in the kernel arguments: no upload
+// launch and no staging slot for a turn's few pages.  One 700-token turn at 48
+// layers (create, prompt write, evict, resume, destroy; 44 pages) went from 105
+// to 85 us with that and with the launches recording the pool's events
+// themselves; eight one-layer resumes of 10,284 pages in all, whose list is
+// uploaded, from 219 to 127 us a resume and eviction.
+struct CopyArgs {
+    PoolGeom src, dst;
+    const CopyEntry* entries;  // device list, or null: `list`
+    int32_t* page_table;
+    int32_t n, chunks_per_entry, chunks_per_slice, by_layer;
+    CopyEntry list[kCopyInline];
+};
+
+template <int U, bool INLINE>
+__global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(const CopyArgs a) {
+    const PoolGeom src = a.src, dst = a.dst;
+    const int32_t n = a.n;
+    const int chunks_per_entry = a.chunks_per_entry, chunks_per_slice = a.chunks_per_slice, by_layer = a.by_layer;
+    int32_t* const page_table = a.page_table;
     const int64_t total = static_cast<int64_t>(n) * chunks_per_entry;
     const int64_t per_layer = static_cast<int64_t>(n) * chunks_per_slice;
     for (int64_t flat = blockIdx.x; flat < total; flat += gridDim.x) {
@@ -83,7 +99,7 @@ __global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(
             layer = chunk / chunks_per_slice;
             cs = chunk % chunks_per_slice;
         }
-        const CopyEntry e = entries[ent];
+        const CopyEntry e = INLINE ? a.list[ent] : a.entries[ent];
         if (layer == 0 && cs == 0 && threadIdx.x == 0 && e.pt_index >= 0) page_table[e.pt_index] = e.pt_value;
         if (e.src < 0) continue;
         const int64_t off = static_cast<int64_t>(cs) * U * kBlockThreads * 16;
@@ -111,6 +127,37 @@ __global__ __launch_bounds__(kBlockThreads) void table_writes_kernel(const CopyE
         const CopyEntry e = entries[i];
         if (e.pt_index >= 0) page_table[e.pt_index] = e.pt_value;
     }
+}
+
+// A list the host wrote to pinned memory, into device memory: one 16-byte load
+// over PCIe per thread.  Latency-bound (a few us for a list of 160 KB) and part
+// of the stream's own queue, where a copy-engine transfer of the same list cost
+// 9 us and 10 to 30 us around it to change engines and back.
+__global__ __launch_bounds__(kBlockThreads) void upload_kernel(const u32x4* __restrict__ host,
+                                                               u32x4* __restrict__ dev, int64_t n16) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x;
+    if (i < n16) dev[i] = __builtin_nontemporal_load(host + i);
+}
+
+// Page-table entries of one row from pinned host memory, read where they lie.
+__global__ __launch_bounds__(kBlockThreads) void upload_row_kernel(const int32_t* __restrict__ host,
+                                                                   int32_t* __restrict__ row, int32_t n) {
+    const int32_t i = static_cast<int32_t>(blockIdx.x * kBlockThreads + threadIdx.x);
+    if (i < n) row[i] = __builtin_nontemporal_load(host + i);
+}
+
+// The same for a short row whose ids are in the kernel arguments.
+__global__ __launch_bounds__(kBlockThreads) void write_row_kernel(const RowArgs a) {
+    for (int32_t i = static_cast<int32_t>(threadIdx.x); i < a.n; i += kBlockThreads) a.row[i] = a.ids[i];
+}
+
+// The first count[r] entries of the page-table rows in the arguments set to -1.
+__global__ __launch_bounds__(kBlockThreads) void clear_rows_kernel(const ClearRowsArgs a) {
+    const int32_t n = a.count[blockIdx.y];
+    int32_t* row = a.page_table + static_cast<int64_t>(a.row[blockIdx.y]) * a.stride;
+    for (int32_t i = static_cast<int32_t>(blockIdx.x * kBlockThreads + threadIdx.x); i < n;
+         i += static_cast<int32_t>(gridDim.x * kBlockThreads))
+        row[i] = -1;
 }
 
 // Streaming read of a whole buffer: each block reads whole chunks of 32 KiB
@@ -457,11 +504,12 @@ int grid_for(int64_t work, int cap) {
 }  // namespace
 
 hipError_t launch_page_copy(const PoolGeom& src, const PoolGeom& dst, int64_t slice_bytes, int32_t layers,
-                            bool by_layer, const CopyEntry* entries, int32_t n, int32_t* page_table,
+                            bool by_layer, const CopyEntry* entries, bool on_host, int32_t n, int32_t* page_table,
                             int32_t max_blocks, hipStream_t s, const LaunchEvents& ev) {
     if (n <= 0) return hipSuccess;
     constexpr int64_t kRow = static_cast<int64_t>(kBlockThreads) * 16;  // 4 KiB
     if (slice_bytes % kRow || slice_bytes <= 0 || layers < 1) return hipErrorInvalidValue;
+    if (on_host && n > kCopyInline) return hipErrorInvalidValue;
     const int64_t rows = slice_bytes / kRow;  // per slice
     // a caller's budget (max_blocks) keeps few blocks: they take the large chunks
     const bool fine = max_blocks <= 0 && rows * layers * n <= HCK_COPY_FINE_ROWS;
@@ -470,18 +518,29 @@ hipError_t launch_page_copy(const PoolGeom& src, const PoolGeom& dst, int64_t sl
                 : (kMaxU >= 8 && rows % 8 == 0) ? 8
                 : (kMaxU >= 4 && rows % 4 == 0) ? 4
                 : (kMaxU >= 2 && rows % 2 == 0) ? 2 : 1;
-    const int cps = static_cast<int>(rows / u);
-    const int cpe = cps * layers;
-    const int64_t work = static_cast<int64_t>(cpe) * n;
+    CopyArgs a;
+    a.src = src;
+    a.dst = dst;
+    a.entries = on_host ? nullptr : entries;
+    a.page_table = page_table;
+    a.n = n;
+    a.chunks_per_slice = static_cast<int>(rows / u);
+    a.chunks_per_entry = a.chunks_per_slice * layers;
+    a.by_layer = by_layer ? 1 : 0;
+    if (on_host)
+        for (int32_t i = 0; i < n; ++i) a.list[i] = entries[i];
+    const int64_t work = static_cast<int64_t>(a.chunks_per_entry) * n;
     const int64_t cap = max_blocks > 0 ? max_blocks : fine ? HCK_COPY_FINE_BLOCKS : HCK_COPY_MAX_BLOCKS;
     const int64_t blocks = work < cap ? work : cap;
-    const void* k = u == 8   ? reinterpret_cast<const void*>(&page_copy_kernel<8>)
-                    : u == 4 ? reinterpret_cast<const void*>(&page_copy_kernel<4>)
-                    : u == 2 ? reinterpret_cast<const void*>(&page_copy_kernel<2>)
-                             : reinterpret_cast<const void*>(&page_copy_kernel<1>);
-    int bl = by_layer ? 1 : 0;
-    void* args[] = {const_cast<PoolGeom*>(&src), const_cast<PoolGeom*>(&dst), &entries, &n,
-                    const_cast<int*>(&cpe), const_cast<int*>(&cps), &bl, &page_table};
+    const void* k = on_host  ? (u == 8   ? reinterpret_cast<const void*>(&page_copy_kernel<8, true>)
+                                : u == 4 ? reinterpret_cast<const void*>(&page_copy_kernel<4, true>)
+                                : u == 2 ? reinterpret_cast<const void*>(&page_copy_kernel<2, true>)
+                                         : reinterpret_cast<const void*>(&page_copy_kernel<1, true>))
+                    : u == 8 ? reinterpret_cast<const void*>(&page_copy_kernel<8, false>)
+                    : u == 4 ? reinterpret_cast<const void*>(&page_copy_kernel<4, false>)
+                    : u == 2 ? reinterpret_cast<const void*>(&page_copy_kernel<2, false>)
+                             : reinterpret_cast<const void*>(&page_copy_kernel<1, false>);
+    void* args[] = {&a};
     return launch_kernel(k, dim3(static_cast<unsigned>(blocks)), dim3(kBlockThreads), args, 0, s, ev);
 }
 
@@ -490,6 +549,39 @@ hipError_t launch_table_writes(const CopyEntry* entries, int32_t n, int32_t* pag
     hipLaunchKernelGGL(table_writes_kernel, dim3(grid_for(n, 1024)), dim3(kBlockThreads), 0, s, entries, n,
                        page_table);
     return hipGetLastError();
+}
+
+hipError_t launch_upload(const void* host, void* dev, size_t bytes, hipStream_t s) {
+    const int64_t n16 = static_cast<int64_t>((bytes + 15) / 16);  // the staging buffers hold whole 16-byte words
+    if (n16 == 0) return hipSuccess;
+    hipLaunchKernelGGL(upload_kernel, dim3(static_cast<unsigned>((n16 + kBlockThreads - 1) / kBlockThreads)),
+                       dim3(kBlockThreads), 0, s, static_cast<const u32x4*>(host), static_cast<u32x4*>(dev), n16);
+    return hipGetLastError();
+}
+
+hipError_t launch_upload_row(const int32_t* host, int32_t* row, int32_t n, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(upload_row_kernel, dim3(static_cast<unsigned>((n + kBlockThreads - 1) / kBlockThreads)),
+                       dim3(kBlockThreads), 0, s, host, row, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_write_row(const RowArgs& a, hipStream_t s) {
+    if (a.n <= 0) return hipSuccess;
+    if (a.n > kRowInline) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(write_row_kernel, dim3(1), dim3(kBlockThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear_rows(const ClearRowsArgs& a, int32_t rows, hipStream_t s, const LaunchEvents& ev) {
+    if (rows <= 0) return hipSuccess;
+    if (rows > kClearRows) return hipErrorInvalidValue;
+    int32_t most = 1;
+    for (int32_t r = 0; r < rows; ++r) most = a.count[r] > most ? a.count[r] : most;
+    void* args[] = {const_cast<ClearRowsArgs*>(&a)};
+    return launch_kernel(reinterpret_cast<const void*>(&clear_rows_kernel),
+                         dim3(static_cast<unsigned>(grid_for(most, 64)), static_cast<unsigned>(rows)),
+                         dim3(kBlockThreads), args, 0, s, ev);
 }
 
 hipError_t launch_read_probe(const void* buf, int64_t bytes, uint32_t* out, int32_t blocks, hipStream_t s) {
