@@ -1233,7 +1233,6 @@ struct WaveWork {
 // combine reads it), then this wave's share; false for waves past the last.
 __device__ __forceinline__ bool wave_work(const DecodeArgs& a, int32_t* s_pref, WaveWork& w) {
     block_prefix_pages<kSplitBlockThreads>(a.seq_lens, a.batch, a.pt_stride, s_pref);
-    __syncthreads();
     if (blockIdx.x == 0)
         for (int b = threadIdx.x; b <= a.batch; b += kSplitBlockThreads) a.row_pref[b] = s_pref[b];
     w.lane = threadIdx.x & (kWave - 1);
@@ -1304,26 +1303,39 @@ __global__ __launch_bounds__(kSplitBlockThreads) void decode_split_valu_kernel(D
 // Merge the partials of one (b, g) for one query head and write its output row.
 // The D/4 lanes of a lane group each own four output dims, and lane groups take
 // every stride-th partial; loads for four partials are issued before any of
-// them is merged.  Narrow: one wave per (b, g, h), four heads per block.  Wide
-// (many partials per segment, i.e. small batches): the block's four waves share
-// one (b, g, h) and merge their results through LDS.  The partials of a segment
-// are those of workers k_first..k_last when there are fewer workers than units,
-// and one per unit (the worker that owns it) otherwise.  Only segments split
-// over several workers have partials (the split writes the others' output
-// itself): the grid walks either all segments, skipping the rest, or, when
-// workers are fewer than segments, the workers' split-segment entries.
-#ifndef HCK_WIDE_COMBINE_PIECES
-#define HCK_WIDE_COMBINE_PIECES 12
-#endif
-constexpr int kWideCombinePieces = HCK_WIDE_COMBINE_PIECES;
+// them is merged.  A head has kWaves waves: one (four heads per block) where
+// segments have few partials, else a block of four or sixteen whose waves merge
+// their results through LDS.  The partials of a segment are those of workers
+// k_first..k_last when there are no more workers than units (each then holds
+// at least one), and one per unit (the worker that owns it) otherwise.  Only
+// segments split over several workers have partials (the split writes the
+// others' output itself): the grid walks either all segments, skipping the
+// rest, or, when workers are fewer than segments, the workers' split-segment
+// entries.  The kernel is a chain of three memory latencies; dropping the
+// 64-bit divisions between them (two of them per partial, for a condition that
+// always holds) and giving long segments sixteen waves took the float32
+// call of 16 ragged rows (48 partials each) from 25.0 to 23.1 us, one row of 32K
+// tokens (192 partials) 11.8 -> 6.9 us in this kernel, and a captured 48-layer step
+// of 8 x 2K tokens, with the shorter prefix sum, 848 -> 804 us.
+constexpr int kWideCombinePieces = 12;   // partials per segment from which four waves share a head
+constexpr int kWidestCombinePieces = 64; // and sixteen
 
-template <int D, bool BF16, bool WIDE>
-__global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArgs a) {
+// ceil-style worker of a unit: the worker that owns unit u - 1, for u >= 1.
+__device__ __forceinline__ int unit_worker(int64_t u, int workers, int64_t total) {
+    if (total * workers <= 0xFFFFFFFFll)
+        return static_cast<int>((static_cast<unsigned>(u) * static_cast<unsigned>(workers) - 1u) /
+                                static_cast<unsigned>(total));
+    return static_cast<int>((u * workers - 1) / total);
+}
+
+template <int D, bool BF16, int kWaves>
+__global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void decode_combine_kernel(DecodeArgs a) {
+    constexpr bool kWide = kWaves > 1;
     constexpr int kQuads = D / 4;
     constexpr int kGroups = kWave / kQuads;
     constexpr int kUnroll = 4;
-    constexpr int kStride = WIDE ? kBlockWaves * kGroups : kGroups;
-    __shared__ float s_merge[WIDE ? kBlockWaves : 1][kQuads][6];
+    constexpr int kStride = kWaves * kGroups;
+    __shared__ float s_merge[kWaves][kQuads][6];
     const int wave = threadIdx.x / kWave;
     const int Lw = a.group_waves;
     const int heads = a.num_kv_heads / Lw;
@@ -1332,7 +1344,7 @@ __global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArg
         // blockIdx.x: a worker; blockIdx.y: (KV head within the head group, head block)
         const int32_t e = a.split_segs[blockIdx.x];
         if (e < 0) return;  // whole block
-        const int ny = WIDE ? a.group : (a.group + kBlockWaves - 1) / kBlockWaves;
+        const int ny = kWide ? a.group : (a.group + kBlockWaves - 1) / kBlockWaves;
         b = e / heads;
         g = (e % heads) * Lw + static_cast<int>(blockIdx.y) / ny;
         hy = static_cast<int>(blockIdx.y) % ny;
@@ -1341,33 +1353,31 @@ __global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArg
         g = static_cast<int>(blockIdx.x) % a.num_kv_heads;
         hy = static_cast<int>(blockIdx.y);
     }
-    const int h = WIDE ? hy : hy * kBlockWaves + wave;
+    const int h = kWide ? hy : hy * kBlockWaves + wave;
     if (h >= a.group) return;  // never taken by a wide block: its grid has one block per head
     const int lane = threadIdx.x & (kWave - 1);
     const int quad = lane % kQuads, grp = lane / kQuads;
-    const int gid = WIDE ? wave * kGroups + grp : grp;
+    const int gid = kWide ? wave * kGroups + grp : grp;
 
     // pages of the rows before b, and of all rows (the split kernel's prefix)
-    const int64_t before = a.row_pref[b], total = a.row_pref[a.batch];
+    const int32_t before = a.row_pref[b], total = a.row_pref[a.batch];
+    const int nb = a.row_pref[b + 1] - before;
     const int32_t len = a.seq_lens[b];
-    const int nb = row_pages(len, a.pt_stride);
     // The split wrote rows with no pages and segments it did not split
     // (uniform over the block: a wide block holds one segment).
     if (nb == 0) return;
     const bool invalid = static_cast<int64_t>(len) > kPageTokens * a.pt_stride;
     // units of head group g / Lw over the workers' ranges; this head's partials
     // are slot (worker + b * heads + g / Lw) * Lw + g % Lw
-    const int64_t sseg = static_cast<int64_t>(b) * heads + g / Lw;
-    const int w_in = g % Lw;
-    const int64_t T = total * heads;
-    const int64_t u_a = before * heads + static_cast<int64_t>(g / Lw) * nb;
+    const int hg = g / Lw, w_in = g - hg * Lw;
+    const int64_t sseg = static_cast<int64_t>(b) * heads + hg;
+    const int64_t T = static_cast<int64_t>(total) * heads;
+    const int64_t u_a = static_cast<int64_t>(before) * heads + static_cast<int64_t>(hg) * nb;
     const int N = a.waves / Lw;
-    const int k_first = static_cast<int>(((u_a + 1) * N - 1) / T);
-    const int k_last = static_cast<int>(((u_a + nb) * N - 1) / T);
+    const int k_first = unit_worker(u_a + 1, N, T);
     const bool per_unit = N > T;  // every non-empty wave holds exactly one unit
-    const int count = per_unit ? nb : k_last - k_first + 1;
+    const int count = per_unit ? nb : unit_worker(u_a + nb, N, T) - k_first + 1;
     if (count == 1) return;
-    f32x4 res;
     float M = -INFINITY, den = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     if (!invalid) {
@@ -1377,11 +1387,9 @@ __global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArg
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int i = i0 + u * kStride;
-                const int k = per_unit ? static_cast<int>(((u_a + i + 1) * N - 1) / T) : k_first + i;
-                // waves whose own unit range is empty wrote nothing to their slot
-                const bool use = i < count &&
-                                 (per_unit || static_cast<int64_t>(k) * T / N != static_cast<int64_t>(k + 1) * T / N);
-                const int64_t slot = (static_cast<int64_t>(use ? k : 0) + sseg) * Lw + w_in;
+                const bool use = i < count;
+                const int k = per_unit && use ? unit_worker(u_a + i + 1, N, T) : k_first + i;
+                const int64_t slot = (static_cast<int64_t>(use ? k : k_first) + sseg) * Lw + w_in;
                 const float* pml = a.part_ml + slot * 2 * a.group;
                 const float m_raw = pml[h], l_raw = pml[a.group + h];
                 const f32x4 o_raw =
@@ -1402,7 +1410,7 @@ __global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArg
             lse_merge(M, den, acc, M2, den2, acc2);
         }
     }
-    if constexpr (WIDE) {
+    if constexpr (kWide) {
         // the block's waves took disjoint partials: merge their results in LDS
         if (grp == 0) {
             float* e = s_merge[wave][quad];
@@ -1414,29 +1422,20 @@ __global__ __launch_bounds__(kBlockThreads) void decode_combine_kernel(DecodeArg
         __syncthreads();
         if (wave != 0) return;
 #pragma unroll
-        for (int w = 1; w < kBlockWaves; ++w) {
+        for (int w = 1; w < kWaves; ++w) {
             const float* e = s_merge[w][quad];
             lse_merge(M, den, acc, e[0], e[1], f32x4{e[2], e[3], e[4], e[5]});
         }
     }
+    f32x4 res;
     if (invalid) {
         const float nan = __builtin_nanf("");
         res = f32x4{nan, nan, nan, nan};
     } else {
         res = BF16 ? acc * (1.0f / den) : acc / den;
     }
-    if (grp == 0) {
-        const int64_t orow =
-            (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad;
-        if constexpr (BF16) {
-            __bf16 v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = static_cast<__bf16>(res[j]);
-            *reinterpret_cast<u32x2*>(static_cast<__bf16*>(a.out) + orow) = __builtin_bit_cast(u32x2, v);
-        } else {
-            *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + orow) = res;
-        }
-    }
+    if (grp == 0)
+        store_quad<D, BF16>(a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad, res);
 }
 
 // Ring depth per shape: the deepest ring that still leaves two (or three)
@@ -1485,18 +1484,19 @@ const void* pick_split(int head_dim, int dtype, bool tiered, bool valu, bool fus
 }
 
 template <int D, bool BF16>
-const void* combine_kernel_ptr(bool wide) {
-    return wide ? reinterpret_cast<const void*>(&decode_combine_kernel<D, BF16, true>)
-                : reinterpret_cast<const void*>(&decode_combine_kernel<D, BF16, false>);
+const void* combine_kernel_ptr(int waves) {
+    return waves == 16  ? reinterpret_cast<const void*>(&decode_combine_kernel<D, BF16, 16>)
+           : waves == 4 ? reinterpret_cast<const void*>(&decode_combine_kernel<D, BF16, 4>)
+                        : reinterpret_cast<const void*>(&decode_combine_kernel<D, BF16, 1>);
 }
 
-const void* pick_combine(int head_dim, int dtype, bool wide) {
+const void* pick_combine(int head_dim, int dtype, int waves) {
     if (dtype == kDtypeBf16) {
-        if (head_dim == 128) return combine_kernel_ptr<128, true>(wide);
-        if (head_dim == 64) return combine_kernel_ptr<64, true>(wide);
+        if (head_dim == 128) return combine_kernel_ptr<128, true>(waves);
+        if (head_dim == 64) return combine_kernel_ptr<64, true>(waves);
     } else {
-        if (head_dim == 128) return combine_kernel_ptr<128, false>(wide);
-        if (head_dim == 64) return combine_kernel_ptr<64, false>(wide);
+        if (head_dim == 128) return combine_kernel_ptr<128, false>(waves);
+        if (head_dim == 64) return combine_kernel_ptr<64, false>(waves);
     }
     return nullptr;
 }
@@ -1525,9 +1525,11 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
     if (segs == 0) return hipSuccess;
     if (a.group_waves < 1 || a.num_kv_heads % a.group_waves || a.waves % a.group_waves)
         return hipErrorInvalidValue;
-    // Many partials per segment (waves well above segments): four waves per head.
-    const bool wide = static_cast<int64_t>(a.waves) >= static_cast<int64_t>(kWideCombinePieces) * segs;
-    const void* k = pick_combine(head_dim, dtype, wide);
+    // Many partials per segment (waves well above segments): several waves per head.
+    const int64_t pieces = a.waves / segs;
+    const int per_head = pieces >= kWidestCombinePieces ? 16 : pieces >= kWideCombinePieces ? 4 : 1;
+    const bool wide = per_head > 1;
+    const void* k = pick_combine(head_dim, dtype, per_head);
     if (!k) return hipErrorInvalidValue;
     const unsigned ny = wide ? static_cast<unsigned>(a.group)
                              : static_cast<unsigned>((a.group + kBlockWaves - 1) / kBlockWaves);
@@ -1539,7 +1541,7 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
     const dim3 grid = c.combine_by_worker
                           ? dim3(static_cast<unsigned>(a.waves / a.group_waves), ny * a.group_waves)
                           : dim3(static_cast<unsigned>(segs), ny);
-    return launch_kernel(k, grid, dim3(kBlockThreads), args, 0, s, ev);
+    return launch_kernel(k, grid, dim3(wide ? per_head * kWave : kBlockThreads), args, 0, s, ev);
 }
 
 int decode_split_blocks_per_cu(int head_dim, int dtype, int batch) {

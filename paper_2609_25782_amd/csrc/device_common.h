@@ -21,39 +21,68 @@ constexpr int kBlockWaves = kBlockThreads / kWave;
 // with a non-positive length occupy none.
 __device__ __forceinline__ int row_pages(int32_t seq_len, int64_t stride) {
     if (seq_len <= 0) return 0;
-    const int64_t n = (static_cast<int64_t>(seq_len) + kPageTokens - 1) / kPageTokens;
-    return static_cast<int>(n < stride ? n : stride);
+    const int n = (seq_len >> 4) + ((seq_len & (kPageTokens - 1)) != 0);
+    const int most = stride < 0x7FFFFFFF ? static_cast<int>(stride) : 0x7FFFFFFF;
+    return n < most ? n : most;
+}
+static_assert(kPageTokens == 16, "row_pages divides by shifting");
+
+// Inclusive sum over the lanes of a wave, in data-parallel primitives: shifts
+// within rows of 16 lanes, then each row's total to the rows after it.
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+    return x;
 }
 
 // s_pref[b] = sum of row_pages over rows < b, for b = 0 .. batch (exclusive
-// prefix sum plus the total).  All kThreads threads of the block must call it;
-// the caller synchronises before reading s_pref.
+// prefix sum plus the total), ready to read when the call returns.  All kThreads
+// threads of the block must call it.  It stands before a decode's first page
+// load.  Up to a wave's worth of rows, every wave sums all of them and writes
+// the same values, so none waits for another; up to a block's worth, each
+// length is read once.
 template <int kThreads = kBlockThreads>
 __device__ inline void block_prefix_pages(const int32_t* __restrict__ seq_lens, int batch,
                                           int64_t stride, int32_t* s_pref) {
-    __shared__ int32_t s_wave_sum[kThreads / kWave];
     const int tid = threadIdx.x;
+    if (batch < kWave) {
+        const int lane = tid & (kWave - 1);
+        const int n = lane < batch ? row_pages(seq_lens[lane], stride) : 0;
+        const int x = wave_scan(n);
+        if (lane <= batch) s_pref[lane] = x - n;
+        __builtin_amdgcn_wave_barrier();
+        return;
+    }
+    __shared__ int32_t s_wave_sum[kThreads / kWave];
     const int per = (batch + kThreads - 1) / kThreads;
     const int lo = min(batch, tid * per);
     const int hi = min(batch, lo + per);
-    int sum = 0;
-    for (int b = lo; b < hi; ++b) sum += row_pages(seq_lens[b], stride);
-    int x = sum;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if ((tid & (kWave - 1)) >= o) x += y;
+    int sum = 0, last = 0;
+    for (int b = lo; b < hi; ++b) {
+        last = row_pages(seq_lens[b], stride);
+        sum += last;
     }
+    const int x = wave_scan(sum);
     if ((tid & (kWave - 1)) == kWave - 1) s_wave_sum[tid / kWave] = x;
     __syncthreads();
     int base = 0;
     for (int w = 0; w < tid / kWave; ++w) base += s_wave_sum[w];
     int run = base + x - sum;
-    for (int b = lo; b < hi; ++b) {
-        s_pref[b] = run;
-        run += row_pages(seq_lens[b], stride);
+    if (per == 1) {
+        if (lo < hi) s_pref[lo] = run;
+        run += last;
+    } else {
+        for (int b = lo; b < hi; ++b) {
+            s_pref[b] = run;
+            run += row_pages(seq_lens[b], stride);
+        }
     }
     if (tid == kThreads - 1) s_pref[batch] = run;
+    __syncthreads();
 }
 
 // One piece of the decode work split: worker `k` handles pages [p0, p1) of

@@ -478,7 +478,6 @@ __global__ __launch_bounds__(kBlockThreads) void partition_kernel(const int32_t*
                                                                   int32_t* slots) {
     extern __shared__ int32_t s_pref[];
     block_prefix_pages(seq_lens, batch, stride, s_pref);
-    __syncthreads();
     const int heads = num_kv_heads / group_waves;
     const int workers = waves / group_waves;
     const int64_t total = static_cast<int64_t>(lds_uniform(s_pref + batch)) * heads;

@@ -72,3 +72,35 @@ def test_append_into_consecutive_short_rows(dev, dtype, D, hq, hkv, waves):
     assert torch.equal(hots[0], hots[1])
     assert torch.equal(outs[0], outs[1])
     tolerance_check(to_host(outs[0]), case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("dtype,D,group", [("bf16", 128, 8), ("bf16", 64, 3), ("f32", 128, 4), ("f32", 64, 16)])
+@pytest.mark.parametrize("waves", [11, 12, 63, 64, 65, 300])
+def test_merge_widths(dev, dtype, D, group, waves):
+    """One row, so `waves` partials per head: one, four and sixteen waves per
+    head merge them, below, at and above the rule's edges."""
+    lens = [16 * 333 - 5]
+    case = Case(1, group, 1, D, dtype, lens, seed=47)
+    pool = build_gpu(case, dev)
+    pool.set_waves(waves)
+    got = to_host(pool.decode(0, to_device(case.q, dtype, dev), torch.tensor(lens, dtype=torch.int32, device=dev)))
+    pool.close()
+    tolerance_check(got, case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("batch", [1, 62, 63, 64, 65, 255, 256, 257, 600])
+def test_row_prefix_of_so_many_rows(dev, batch):
+    """The prefix sum of a wave's worth of rows, of a block's worth and of more,
+    empty rows among them; the partition table uses the same sum."""
+    from oracle import partition
+    rng = np.random.default_rng(batch)
+    lens = [int(x) for x in rng.integers(0, 70, size=batch)]
+    lens[-1] = 33
+    case = Case(1, 4, 2, 64, "bf16", lens, seed=53)
+    pool = build_gpu(case, dev)
+    sl = torch.tensor(lens, dtype=torch.int32, device=dev)
+    got = to_host(pool.decode(0, to_device(case.q, "bf16", dev), sl))
+    slots = pool.partition(sl, 24).cpu().numpy()
+    pool.close()
+    tolerance_check(got, case.oracle_out())
+    assert np.array_equal(slots, np.array(partition.slot_table(lens, 2, 24), dtype=np.int32))
