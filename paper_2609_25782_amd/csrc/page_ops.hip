@@ -64,26 +64,10 @@ __device__ __forceinline__ char* entry_slice(const PoolGeom& hot, const PoolGeom
 // it at a time, which address translation serves far better than slices
 // spread over the whole pool (reads stall on it; the scattered writes of the
 // other direction are posted and hurt less).
-// Short lists (kCopyInline entries) travel in the kernel arguments: no upload
-// launch and no staging slot for a turn's few pages.  One 700-token turn at 48
-// layers (create, prompt write, evict, resume, destroy; 44 pages) went from 105
-// to 85 us with that and with the launches recording the pool's events
-// themselves; eight one-layer resumes of 10,284 pages in all, whose list is
-// uploaded, from 219 to 127 us a resume and eviction.
-struct CopyArgs {
-    PoolGeom src, dst;
-    const CopyEntry* entries;  // device list, or null: `list`
-    int32_t* page_table;
-    int32_t n, chunks_per_entry, chunks_per_slice, by_layer;
-    CopyEntry list[kCopyInline];
-};
-
-template <int U, bool INLINE>
-__global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(const CopyArgs a) {
-    const PoolGeom src = a.src, dst = a.dst;
-    const int32_t n = a.n;
-    const int chunks_per_entry = a.chunks_per_entry, chunks_per_slice = a.chunks_per_slice, by_layer = a.by_layer;
-    int32_t* const page_table = a.page_table;
+template <int U, typename Entries>
+__device__ __forceinline__ void copy_pages(const PoolGeom& src, const PoolGeom& dst, const Entries& entries, int32_t n,
+                                           int chunks_per_entry, int chunks_per_slice, int by_layer,
+                                           int32_t* __restrict__ page_table) {
     const int64_t total = static_cast<int64_t>(n) * chunks_per_entry;
     const int64_t per_layer = static_cast<int64_t>(n) * chunks_per_slice;
     for (int64_t flat = blockIdx.x; flat < total; flat += gridDim.x) {
@@ -99,7 +83,7 @@ __global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(const CopyArgs
             layer = chunk / chunks_per_slice;
             cs = chunk % chunks_per_slice;
         }
-        const CopyEntry e = INLINE ? a.list[ent] : a.entries[ent];
+        const CopyEntry e = entries[ent];
         if (layer == 0 && cs == 0 && threadIdx.x == 0 && e.pt_index >= 0) page_table[e.pt_index] = e.pt_value;
         if (e.src < 0) continue;
         const int64_t off = static_cast<int64_t>(cs) * U * kBlockThreads * 16;
@@ -118,6 +102,35 @@ __global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(const CopyArgs
                 d[i * kBlockThreads] = buf[i];
         }
     }
+}
+
+// The list is a __restrict__ argument of its own: blocks that share an entry
+// then read it through the scalar cache.  As a member of a struct it came
+// through the vector path, one more memory latency in each 4 KiB block: 131
+// against 108 us for 337 MB of one-layer pages.
+template <int U>
+__global__ __launch_bounds__(kBlockThreads) void page_copy_kernel(
+    const PoolGeom src, const PoolGeom dst, const CopyEntry* __restrict__ entries, int32_t n,
+    int chunks_per_entry, int chunks_per_slice, int by_layer, int32_t* __restrict__ page_table) {
+    copy_pages<U>(src, dst, entries, n, chunks_per_entry, chunks_per_slice, by_layer, page_table);
+}
+
+// Short lists (kCopyInline entries) travel in the kernel arguments: no upload
+// launch and no staging slot for a turn's few pages.  One 700-token turn at 48
+// layers (create, prompt write, evict, resume, destroy; 44 pages) went from 105
+// to 85 us with that and with the launches recording the pool's events
+// themselves; eight one-layer resumes of 10,284 pages in all, whose list is
+// uploaded, from 219 to 127 us a resume and eviction.
+struct CopyList {
+    CopyEntry e[kCopyInline];
+    __device__ const CopyEntry& operator[](int i) const { return e[i]; }
+};
+
+template <int U>
+__global__ __launch_bounds__(kBlockThreads) void page_copy_inline_kernel(
+    const PoolGeom src, const PoolGeom dst, int32_t n, int chunks_per_entry, int chunks_per_slice, int by_layer,
+    int32_t* __restrict__ page_table, const CopyList list) {
+    copy_pages<U>(src, dst, list, n, chunks_per_entry, chunks_per_slice, by_layer, page_table);
 }
 
 __global__ __launch_bounds__(kBlockThreads) void table_writes_kernel(const CopyEntry* __restrict__ entries,
@@ -517,30 +530,30 @@ hipError_t launch_page_copy(const PoolGeom& src, const PoolGeom& dst, int64_t sl
                 : (kMaxU >= 8 && rows % 8 == 0) ? 8
                 : (kMaxU >= 4 && rows % 4 == 0) ? 4
                 : (kMaxU >= 2 && rows % 2 == 0) ? 2 : 1;
-    CopyArgs a;
-    a.src = src;
-    a.dst = dst;
-    a.entries = on_host ? nullptr : entries;
-    a.page_table = page_table;
-    a.n = n;
-    a.chunks_per_slice = static_cast<int>(rows / u);
-    a.chunks_per_entry = a.chunks_per_slice * layers;
-    a.by_layer = by_layer ? 1 : 0;
-    if (on_host)
-        for (int32_t i = 0; i < n; ++i) a.list[i] = entries[i];
-    const int64_t work = static_cast<int64_t>(a.chunks_per_entry) * n;
+    const int cps = static_cast<int>(rows / u);
+    const int cpe = cps * layers;
+    const int64_t work = static_cast<int64_t>(cpe) * n;
     const int64_t cap = max_blocks > 0 ? max_blocks : fine ? HCK_COPY_FINE_BLOCKS : HCK_COPY_MAX_BLOCKS;
-    const int64_t blocks = work < cap ? work : cap;
-    const void* k = on_host  ? (u == 8   ? reinterpret_cast<const void*>(&page_copy_kernel<8, true>)
-                                : u == 4 ? reinterpret_cast<const void*>(&page_copy_kernel<4, true>)
-                                : u == 2 ? reinterpret_cast<const void*>(&page_copy_kernel<2, true>)
-                                         : reinterpret_cast<const void*>(&page_copy_kernel<1, true>))
-                    : u == 8 ? reinterpret_cast<const void*>(&page_copy_kernel<8, false>)
-                    : u == 4 ? reinterpret_cast<const void*>(&page_copy_kernel<4, false>)
-                    : u == 2 ? reinterpret_cast<const void*>(&page_copy_kernel<2, false>)
-                             : reinterpret_cast<const void*>(&page_copy_kernel<1, false>);
-    void* args[] = {&a};
-    return launch_kernel(k, dim3(static_cast<unsigned>(blocks)), dim3(kBlockThreads), args, 0, s, ev);
+    const dim3 grid(static_cast<unsigned>(work < cap ? work : cap));
+    int bl = by_layer ? 1 : 0;
+    if (on_host) {
+        const void* k = u == 8   ? reinterpret_cast<const void*>(&page_copy_inline_kernel<8>)
+                        : u == 4 ? reinterpret_cast<const void*>(&page_copy_inline_kernel<4>)
+                        : u == 2 ? reinterpret_cast<const void*>(&page_copy_inline_kernel<2>)
+                                 : reinterpret_cast<const void*>(&page_copy_inline_kernel<1>);
+        CopyList list = {};
+        for (int32_t i = 0; i < n; ++i) list.e[i] = entries[i];
+        void* args[] = {const_cast<PoolGeom*>(&src), const_cast<PoolGeom*>(&dst), &n, const_cast<int*>(&cpe),
+                        const_cast<int*>(&cps), &bl, &page_table, &list};
+        return launch_kernel(k, grid, dim3(kBlockThreads), args, 0, s, ev);
+    }
+    const void* k = u == 8   ? reinterpret_cast<const void*>(&page_copy_kernel<8>)
+                    : u == 4 ? reinterpret_cast<const void*>(&page_copy_kernel<4>)
+                    : u == 2 ? reinterpret_cast<const void*>(&page_copy_kernel<2>)
+                             : reinterpret_cast<const void*>(&page_copy_kernel<1>);
+    void* args[] = {const_cast<PoolGeom*>(&src), const_cast<PoolGeom*>(&dst), &entries, &n,
+                    const_cast<int*>(&cpe), const_cast<int*>(&cps), &bl, &page_table};
+    return launch_kernel(k, grid, dim3(kBlockThreads), args, 0, s, ev);
 }
 
 hipError_t launch_table_writes(const CopyEntry* entries, int32_t n, int32_t* page_table, hipStream_t s) {
