@@ -1518,7 +1518,6 @@ size_t paged_decode_workspace_bytes(const kv_pool* pool, int32_t batch, int32_t 
     if (!pool || pool->meta || batch < 0 || num_q_heads <= 0 || num_q_heads % pool->d.num_kv_heads)
         return 0;
     const int32_t group = num_q_heads / pool->d.num_kv_heads;
-    DeviceGuard g(pool->d.device);
     const int32_t waves = pool->decode_waves();
     const int64_t slots = static_cast<int64_t>(waves) + static_cast<int64_t>(batch) * pool->d.num_kv_heads;
     return hck::decode_workspace_bytes(slots, group, pool->d.head_dim, batch, waves);
