@@ -616,14 +616,113 @@ __device__ __forceinline__ void append_in_place(PageRegs<D, BF16>& pg, const Tok
     }
 }
 
+// Order this wave's LDS accesses: earlier writes complete before later reads,
+// and the compiler moves no LDS access across it.
+__device__ __forceinline__ void wave_lds_sync() { __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Holding results in LDS (calls with many rows: HOLD).  The counter that a
+// wave's loads are waited for with also counts its stores, in order, and a store
+// between the pages' reads is acknowledged late: each row written where it ended
+// cost 2.4 us of the wave's stream (a ring run empty), a partial as much.  So a
+// wave keeps the rows that it finishes in LDS, `out_slots` of them, and writes
+// them together, as full 1 KiB stores, when the slots are full and when its
+// range ends; the partial of the segment that its range starts inside of waits
+// for the end too.  1,024 rows of 512 tokens: 186.7 -> 167.8 us a call, of 256 to
+// 768 tokens 189 -> 168 us, of 1,500 on average 498 -> 466 us (6.9 TB/s); 512
+// rows of 8 KV heads, 512 tokens on average, 183 -> 177 us; float32 192 -> 182 us.
+constexpr int kLdsBudget = 60 << 10;  // of a 64 KiB launch, a few words of it static
+constexpr int kMaxOutSlots = 8;
+template <int D>
+constexpr int kPartialBytes = 8 * (4 * D + 16);  // float32 rows of eight heads, 16 bytes past each other's banks
+
+// Bytes of one slot: the group's output rows, laid out likewise.
+__host__ __device__ __forceinline__ int out_slot_bytes(int group, int row_bytes) { return group * (row_bytes + 16); }
+
+// A lane holds head lane % 16, dims 16 c + 4 (lane / 16) .. + 3 of chunk c,
+// given by val(c): the group's rows into LDS.
+template <int D, bool BF16, typename Val>
+__device__ __forceinline__ void stage_heads(char* stage, int group, int lane, Val val) {
+    constexpr int kElt = BF16 ? 2 : 4, kPitch = D * kElt + 16;
+    if ((lane & 15) < group) {
+        char* row = stage + (lane & 15) * kPitch + 4 * (lane >> 4) * kElt;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+            const f32x4 x = val(c);
+            if constexpr (BF16) {
+                __bf16 v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = static_cast<__bf16>(x[j]);
+                *reinterpret_cast<u32x2*>(row + 16 * c * kElt) = __builtin_bit_cast(u32x2, v);
+            } else {
+                *reinterpret_cast<f32x4*>(row + 16 * c * kElt) = x;
+            }
+        }
+    }
+}
+
+// The staged rows to dst, where they follow each other.
+template <int D, bool BF16>
+__device__ __forceinline__ void write_heads(void* dst, const char* stage, int group, int lane) {
+    constexpr int kRow = D * (BF16 ? 2 : 4), kPitch = kRow + 16;
+    for (int o = 16 * lane; o < group * kRow; o += 16 * kWave)
+        *reinterpret_cast<u32x4*>(static_cast<char*>(dst) + o) =
+            *reinterpret_cast<const u32x4*>(stage + o / kRow * kPitch + o % kRow);
+}
+
+// What a wave holds: LDS with the partial's place, then the slots.
+template <int D, bool BF16>
+struct Held {
+    static constexpr int kRow = D * Shape<D, BF16>::kElt;
+    char* lds;
+    int rows = 0;          // slots in use
+    int row_seg = -1;      // lane i: the segment (b * KV heads + KV head) in slot i
+    int part_slot = -1;    // the partial's slot in the workspace, or -1
+    float part_m, part_l;
+
+    __device__ __forceinline__ char* slot(const DecodeArgs& a, int i) const {
+        return lds + kPartialBytes<D> + i * out_slot_bytes(a.group, kRow);
+    }
+
+    __device__ __forceinline__ void write_rows(const DecodeArgs& a, int lane) {
+        wave_lds_sync();
+        for (int i = 0; i < rows; ++i) {
+            const int64_t seg = __builtin_amdgcn_readlane(row_seg, i);
+            write_heads<D, BF16>(static_cast<char*>(a.out) + seg * a.group * kRow, slot(a, i), a.group, lane);
+        }
+        wave_lds_sync();
+        rows = 0;
+    }
+
+    template <typename Val>
+    __device__ __forceinline__ void row(const DecodeArgs& a, int seg, int lane, Val val) {
+        if (rows == a.out_slots) write_rows(a, lane);
+        stage_heads<D, BF16>(slot(a, rows), a.group, lane, val);
+        row_seg = lane == rows ? seg : row_seg;
+        ++rows;
+    }
+
+    __device__ __forceinline__ void write_all(const DecodeArgs& a, int lane) {
+        if (part_slot >= 0) {
+            wave_lds_sync();
+            write_heads<D, false>(a.part_o + static_cast<int64_t>(part_slot) * a.group * D, lds, a.group, lane);
+            if (lane < a.group) {
+                float* pml = a.part_ml + static_cast<int64_t>(part_slot) * 2 * a.group;
+                pml[lane] = part_m;
+                pml[a.group + lane] = part_l;
+            }
+        }
+        if (rows > 0) write_rows(a, lane);
+    }
+};
+
 // A piece's result: the output rows themselves when the piece is its whole
 // segment, else a partial (running max, weight sum, unnormalised output).
-template <int D, bool BF16, bool FUSED>
-__device__ __forceinline__ void finish_piece(const DecodeArgs& a, SegmentState<D, BF16>& st, unsigned word,
-                                             bool whole, bool bad, int worker, int heads, int w_in, int lane) {
+template <int D, bool BF16, bool FUSED, bool HOLD>
+__device__ __forceinline__ void finish_piece(const DecodeArgs& a, Held<D, BF16>& held, SegmentState<D, BF16>& st,
+                                             unsigned word, bool whole, bool bad, int worker, int heads, int w_in,
+                                             int lane) {
     using S = Shape<D, BF16>;
     const int h = lane & 15, qg = lane >> 4;
-    const bool hvalid = h < a.group;
     const int b = static_cast<int>(word & kUnitRowMask), hg = static_cast<int>((word >> kUnitGroupShift) & 15u);
     const int g = hg * a.group_waves + w_in;
     float l = wave_sum_4(st.l);
@@ -632,21 +731,27 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, SegmentState<D
         // (o + 0) / l is what merging this one partial gives.  A head's lanes
         // share l, so bf16 results take one division and multiply by it: the
         // last float32 bit is far below bf16's rounding.
-        if (hvalid) {
-            const float nan = __builtin_nanf("");
-            const bool row_invalid = (word & kUnitRowInvalid) != 0;
+        if (word & kUnitRowInvalid) l = __builtin_nanf("");
+        const float inv = 1.0f / l;
+        auto val = [&](int c) { return BF16 ? (st.o[c] + 0.f) * inv : (st.o[c] + 0.f) / l; };
+        if constexpr (HOLD) {
+            held.row(a, b * a.num_kv_heads + g, lane, val);
+        } else if (h < a.group) {
             const int64_t orow = (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * qg;
-            const float inv = 1.0f / l;
 #pragma unroll
-            for (int c = 0; c < S::kChunks; ++c) {
-                const f32x4 res = BF16 ? (st.o[c] + 0.f) * inv : (st.o[c] + 0.f) / l;
-                store_quad<D, BF16>(a, orow + 16 * c, row_invalid ? f32x4{nan, nan, nan, nan} : res);
-            }
+            for (int c = 0; c < S::kChunks; ++c) store_quad<D, BF16>(a, orow + 16 * c, val(c));
         }
         return;
     }
-    if (hvalid) {
-        const int64_t slot = (static_cast<int64_t>(worker) + static_cast<int64_t>(b) * heads + hg) * a.group_waves + w_in;
+    const int64_t slot = (static_cast<int64_t>(worker) + static_cast<int64_t>(b) * heads + hg) * a.group_waves + w_in;
+    if (HOLD && (word & kUnitSegLast) && a.group <= 8) {  // the range's first piece, at most one
+        stage_heads<D, false>(held.lds, a.group, lane, [&](int c) { return st.o[c]; });
+        held.part_m = st.m;
+        held.part_l = l;
+        held.part_slot = static_cast<int>(slot);
+        return;
+    }
+    if (h < a.group) {
         float* po = a.part_o + (slot * a.group + h) * D + 4 * qg;
         float* pml = a.part_ml + slot * 2 * a.group;
         if constexpr (FUSED) {
@@ -723,9 +828,9 @@ __device__ void merge_ends(const DecodeArgs& a, const int32_t* s_pref, const Spl
 // us; 1,024 rows of 512 tokens 196 -> 187 us; 32 rows of 8K-32K tokens 211.8 ->
 // 208.9 us (6.70 TB/s); a captured 48-layer step of 8 x 2K tokens with the fused
 // append 955 -> 848 us.
-template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND>
+template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND, bool HOLD>
 __device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_t* s_pref, int64_t u0, int64_t u1,
-                                               int worker, int heads, int w_in, int lane) {
+                                               int worker, int heads, int w_in, int lane, char* lds) {
     using S = Shape<D, BF16>;
     constexpr int kChunk = kWave / R * R;  // units per chunk: whole rounds of the ring
     SplitEnds ends;
@@ -798,6 +903,8 @@ __device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_
     };
 
     SegmentState<D, BF16> st;
+    Held<D, BF16> held;
+    held.lds = lds;
     bool bad = false, seg_first = false;
     // What a unit needs besides its page, taken before the step's own loads go
     // out: those may load the next queries or token into the same registers.
@@ -851,7 +958,7 @@ __device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_
                 ends.last = seg;
                 ends.last_starts = seg_first;
             }
-            finish_piece<D, BF16, FUSED>(a, st, w, seg_first && seg_last, bad, worker, heads, w_in, lane);
+            finish_piece<D, BF16, FUSED, HOLD>(a, held, st, w, seg_first && seg_last, bad, worker, heads, w_in, lane);
         }
     };
 
@@ -871,6 +978,7 @@ __device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_
             }
         }
     }
+    if constexpr (HOLD) held.write_all(a, lane);
     return ends;
 }
 
@@ -902,10 +1010,6 @@ struct ValuState {
     float o[kValuMaxGroup][D / 16];  // lane (dl, qg): head h, dim 16 c + dl, over tokens 4 qg .. + 3
     float m[2], l[2];                // lane (t, qq): heads 2 qq + e; l over token t only
 };
-
-// Order this wave's LDS accesses: earlier writes complete before later reads,
-// and the compiler moves no LDS access across it.
-__device__ __forceinline__ void wave_lds_sync() { __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ float dot2_bf16(unsigned a, unsigned b, float c) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -1222,6 +1326,14 @@ constexpr int split_waves_per_eu() {
     return D == 128 && (!BF16 || FUSED) ? 1 : 2;
 }
 
+// Dynamic LDS of the split: the row prefix, then (HOLD) what each wave holds.
+__host__ __device__ __forceinline__ int prefix_lds_bytes(int batch) { return (4 * (batch + 1) + 15) & ~15; }
+
+template <int D>
+__host__ __device__ __forceinline__ int held_lds_bytes(int group, int row_bytes, int out_slots) {
+    return kPartialBytes<D> + out_slots * out_slot_bytes(group, row_bytes);
+}
+
 // What a wave of the split works on: its worker, its KV head within the
 // worker's head group and its units [u0, u1).
 struct WaveWork {
@@ -1258,14 +1370,16 @@ __device__ __forceinline__ void fill_empty_rows(const DecodeArgs& a, const int32
     }
 }
 
-template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND>
+template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND, bool HOLD>
 __global__ __launch_bounds__(kSplitBlockThreads)
 __attribute__((amdgpu_waves_per_eu(split_waves_per_eu<D, BF16, FUSED>()))) void decode_split_kernel(DecodeArgs a) {
     extern __shared__ int32_t s_pref[];
     WaveWork w;
     if (!wave_work(a, s_pref, w)) return;
-    const SplitEnds ends =
-        run_units<D, BF16, R, TIERED, FUSED, APPEND>(a, s_pref, w.u0, w.u1, w.worker, w.heads, w.w_in, w.lane);
+    const SplitEnds ends = run_units<D, BF16, R, TIERED, FUSED, APPEND, HOLD>(
+        a, s_pref, w.u0, w.u1, w.worker, w.heads, w.w_in, w.lane,
+        reinterpret_cast<char*>(s_pref) + prefix_lds_bytes(a.batch) +
+            threadIdx.x / kWave * held_lds_bytes<D>(a.group, D * Shape<D, BF16>::kElt, a.out_slots));
     if constexpr (FUSED)
         merge_ends<D, BF16>(a, s_pref, ends, w.heads, w.w_in, w.total, w.lane);
     else if (w.w_in == 0 && w.lane == 0)
@@ -1445,19 +1559,21 @@ constexpr int ring_depth() {
     return BF16 ? (D == 128 ? HCK_RING_BF16_D128 : 5) : (D == 128 ? 2 : 3);
 }
 
-template <int D, bool BF16, bool TIERED>
-const void* split_kernel_ptr(bool fused, bool append) {
+enum class Merge { kFused, kSeparate, kSeparateHold };  // how the split's results go out
+
+template <int D, bool BF16, bool TIERED, bool APPEND>
+const void* split_kernel_ptr(Merge m) {
     constexpr int R = ring_depth<D, BF16>();
-    if (fused)
-        return append ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, true, true>)
-                      : reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, true, false>);
-    return append ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, false, true>)
-                  : reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, false, false>);
+    return m == Merge::kFused ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, true, APPEND, false>)
+           : m == Merge::kSeparate
+               ? reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, false, APPEND, false>)
+               : reinterpret_cast<const void*>(&decode_split_kernel<D, BF16, R, TIERED, false, APPEND, true>);
 }
 
 template <int D, bool BF16>
-const void* split_kernel_ptr(bool tiered, bool fused, bool append) {
-    return tiered ? split_kernel_ptr<D, BF16, true>(fused, append) : split_kernel_ptr<D, BF16, false>(fused, append);
+const void* split_kernel_ptr(bool tiered, bool append, Merge m) {
+    if (tiered) return append ? split_kernel_ptr<D, BF16, true, true>(m) : split_kernel_ptr<D, BF16, true, false>(m);
+    return append ? split_kernel_ptr<D, BF16, false, true>(m) : split_kernel_ptr<D, BF16, false, false>(m);
 }
 
 template <int D>
@@ -1468,17 +1584,17 @@ const void* valu_kernel_ptr(bool tiered) {
 }
 
 // The vector-ALU variant exists for bf16 only.
-const void* pick_split(int head_dim, int dtype, bool tiered, bool valu, bool fused, bool append) {
+const void* pick_split(int head_dim, int dtype, bool tiered, bool valu, bool append, Merge m) {
     if (valu) {
         if (dtype != kDtypeBf16) return nullptr;
         return head_dim == 128 ? valu_kernel_ptr<128>(tiered) : head_dim == 64 ? valu_kernel_ptr<64>(tiered) : nullptr;
     }
     if (dtype == kDtypeBf16) {
-        if (head_dim == 128) return split_kernel_ptr<128, true>(tiered, fused, append);
-        if (head_dim == 64) return split_kernel_ptr<64, true>(tiered, fused, append);
+        if (head_dim == 128) return split_kernel_ptr<128, true>(tiered, append, m);
+        if (head_dim == 64) return split_kernel_ptr<64, true>(tiered, append, m);
     } else {
-        if (head_dim == 128) return split_kernel_ptr<128, false>(tiered, fused, append);
-        if (head_dim == 64) return split_kernel_ptr<64, false>(tiered, fused, append);
+        if (head_dim == 128) return split_kernel_ptr<128, false>(tiered, append, m);
+        if (head_dim == 64) return split_kernel_ptr<64, false>(tiered, append, m);
     }
     return nullptr;
 }
@@ -1501,8 +1617,6 @@ const void* pick_combine(int head_dim, int dtype, int waves) {
     return nullptr;
 }
 
-size_t prefix_lds_bytes(int batch) { return static_cast<size_t>(batch + 1) * sizeof(int32_t); }
-
 }  // namespace
 
 hipError_t launch_decode_split(const DecodeArgs& a, int head_dim, int dtype, hipStream_t s,
@@ -1512,11 +1626,35 @@ hipError_t launch_decode_split(const DecodeArgs& a, int head_dim, int dtype, hip
     if (a.group_waves < 1 || kSplitBlockWaves % a.group_waves || a.num_kv_heads % a.group_waves ||
         a.waves % a.group_waves)
         return hipErrorInvalidValue;
-    const void* k = pick_split(head_dim, dtype, a.tiered != 0, a.valu != 0, a.fused != 0, a.k_new != nullptr);
-    if (!k || a.waves <= 0) return hipErrorInvalidValue;
+    if (a.waves <= 0 || (head_dim != 64 && head_dim != 128)) return hipErrorInvalidValue;
     const int blocks = (a.waves + kSplitBlockWaves - 1) / kSplitBlockWaves;
-    void* args[] = {const_cast<DecodeArgs*>(&a)};
-    return launch_kernel(k, dim3(blocks), dim3(kSplitBlockThreads), args, prefix_lds_bytes(a.batch), s, ev);
+    DecodeArgs c = a;
+    c.out_slots = 0;
+    int lds = prefix_lds_bytes(a.batch);
+    Merge merge = a.fused ? Merge::kFused : Merge::kSeparate;
+    // Results are held in LDS where segments (row, head group) are no fewer than
+    // workers, so that waves finish whole rows, and where a segment's rows are at
+    // least 1 KiB.  Below the first line nearly all segments are split, and the
+    // larger kernel costs short calls up to 1% (8 x 2K); below the second a row
+    // costs as much to hold as to store (16 heads of 64 dims, one query head
+    // each: 1% slower).  As many slots as the budget leaves room for; no holding
+    // without at least two (thousands of rows with wide groups).
+    const int row = head_dim * (dtype == kDtypeBf16 ? 2 : 4);
+    if (!a.valu && !a.fused && a.group * row >= 1024 &&
+        static_cast<int64_t>(a.batch) * a.num_kv_heads >= a.waves) {
+        const int slot = out_slot_bytes(a.group, row);
+        const int base = head_dim == 128 ? held_lds_bytes<128>(a.group, row, 0) : held_lds_bytes<64>(a.group, row, 0);
+        const int room = ((kLdsBudget - lds) / kSplitBlockWaves - base) / slot;
+        if (room >= 2) {
+            merge = Merge::kSeparateHold;
+            c.out_slots = room < kMaxOutSlots ? room : kMaxOutSlots;
+            lds += kSplitBlockWaves * (base + c.out_slots * slot);
+        }
+    }
+    const void* k = pick_split(head_dim, dtype, a.tiered != 0, a.valu != 0, a.k_new != nullptr, merge);
+    if (!k) return hipErrorInvalidValue;
+    void* args[] = {&c};
+    return launch_kernel(k, dim3(blocks), dim3(kSplitBlockThreads), args, lds, s, ev);
 }
 
 hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, hipStream_t s,
@@ -1545,7 +1683,7 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
 }
 
 int decode_split_blocks_per_cu(int head_dim, int dtype, int batch) {
-    const void* k = pick_split(head_dim, dtype, false, false, false, false);
+    const void* k = pick_split(head_dim, dtype, false, false, false, Merge::kSeparate);
     if (!k) return 0;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kSplitBlockThreads, prefix_lds_bytes(batch)) !=

@@ -71,6 +71,7 @@ struct DecodeArgs {
     const char* stage;        // staging buffer of this layer: [slot][kv_head][K tile, V tile]
     int32_t num_stage_slots;
     int64_t slice_bytes;      // bytes of one staging slot
+    int32_t out_slots;        // finished rows a wave holds in LDS (set by the split launch)
     int32_t valu;             // 1: the split runs its products on the vector ALU (bf16, group <= 8)
     // Fused append (nullable): row b's token L - 1, [batch][num_kv_heads][head_dim], written
     // into its page before the page is read.

@@ -104,3 +104,37 @@ def test_row_prefix_of_so_many_rows(dev, batch):
     pool.close()
     tolerance_check(got, case.oracle_out())
     assert np.array_equal(slots, np.array(partition.slot_table(lens, 2, 24), dtype=np.int32))
+
+
+@pytest.mark.parametrize("dtype,D,hq,hkv,batch", [
+    ("bf16", 128, 32, 4, 90),    # the model's shape: rows of 2 KiB per KV head
+    ("bf16", 128, 16, 1, 90),    # 16 heads per group: the partial is not held
+    ("bf16", 64, 16, 2, 90),     # 1 KiB exactly
+    ("bf16", 64, 14, 2, 90),     # below 1 KiB: rows stored as they end
+    ("f32", 128, 8, 1, 90),      # two slots
+    ("f32", 128, 16, 1, 90),     # room for one slot only: rows stored as they end
+    ("bf16", 128, 8, 1, 5000),   # the row prefix takes 20 KB of the LDS
+])
+@pytest.mark.parametrize("waves", [3, 4, 8])
+def test_rows_held_until_slots_fill(dev, dtype, D, hq, hkv, batch, waves):
+    """More segments than waves: each wave finishes many whole rows, more than it
+    can hold at once, among them empty rows and one bad page id (a NaN row).
+    The output starts as NaN: every row must be written."""
+    rng = np.random.default_rng(batch + waves)
+    lens = [int(x) for x in (rng.integers(1, 120, size=batch) if batch < 1000 else rng.integers(1, 18, size=batch))]
+    lens[4] = lens[5] = 0
+    case = Case(1, hq, hkv, D, dtype, lens, seed=59)
+    pool = build_gpu(case, dev, poison=True)
+    pool.set_waves(waves)
+    q = to_device(case.q, dtype, dev)
+    table = pool.page_table.clone()
+    table[7, 0] = case.hot_pages
+    out = torch.full_like(q, float("nan"))
+    pool.decode(0, q, torch.tensor(lens, dtype=torch.int32, device=dev), page_table=table, out=out)
+    got = to_host(out)
+    pool.close()
+    assert np.isnan(got[7]).all()
+    assert (got[4:6] == 0).all()
+    rows = [b for b in range(batch) if lens[b] and b != 7][:: max(1, batch // 300)]
+    rowwise_check(got[rows], case.oracle_out(rows=rows), max_norm=1e-2 if dtype == "bf16" else 1e-5)
+    assert np.isfinite(np.delete(got, 7, axis=0)).all()
