@@ -312,13 +312,16 @@ __device__ __forceinline__ void write_token_group(char* lh, int64_t tile, int sl
                                                   const char* ksrc, const char* vsrc) {
     *reinterpret_cast<u32x4*>(lh + (static_cast<int64_t>(cd) * kPageTokens + slot) * x * elt) =
         *reinterpret_cast<const u32x4*>(ksrc);
-    char* vt = lh + tile;
-    for (int j = 0; j < x; ++j) {
-        const int64_t e = static_cast<int64_t>(cd * x + j) * kPageTokens + slot;
-        if (elt == 2)
-            *reinterpret_cast<unsigned short*>(vt + e * 2) = reinterpret_cast<const unsigned short*>(vsrc)[j];
-        else
-            *reinterpret_cast<unsigned*>(vt + e * 4) = reinterpret_cast<const unsigned*>(vsrc)[j];
+    const u32x4 v = *reinterpret_cast<const u32x4*>(vsrc);
+    char* vt = lh + tile + (static_cast<int64_t>(cd) * x * kPageTokens + slot) * elt;
+    if (elt == 2) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<unsigned short*>(vt + j * kPageTokens * 2) =
+                static_cast<unsigned short>(v[j / 2] >> (16 * (j & 1)));
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<unsigned*>(vt + j * kPageTokens * 4) = v[j];
     }
 }
 
@@ -404,59 +407,65 @@ __global__ __launch_bounds__(kBlockThreads) void write_tokens_kernel(WriteArgs a
     }
 }
 
-// Row r of the batch: one token into page e[r].page (a hot id, or a cold id
+// The appends are a chain of latencies (the entry or the row's page id, then
+// the token, then its stores), so nothing else stands in it: a block is one
+// row, thread t is 16-byte group t % groups of KV head t / groups, and groups
+// is a power of two.
+// With one flat index and 64-bit divisions it took 5.1 us for 32 rows, now 4.2; an
+// eager 48-layer step of 32 x 4K tokens that appends in every layer 2530 -> 2431 us.
+struct AppendThread {
+    int head, cd;
+};
+__device__ __forceinline__ AppendThread append_thread(int t, int groups) {
+    const int shift = 31 - __clz(groups);
+    return AppendThread{t >> shift, t & (groups - 1)};
+}
+
+// Row blockIdx.x of the batch: one token into page e[r].page (a hot id, or a cold id
 // tagged KV_PAGE_COLD) at slot e[r].slot; K and V rows [n][kv_heads][head_dim].
 __global__ __launch_bounds__(kBlockThreads) void append_tokens_kernel(const AppendArgs a) {
     const int elt = a.dtype == kDtypeBf16 ? 2 : 4;
     const int x = 16 / elt;
     const int groups = a.head_dim / x;
     const int64_t tile = static_cast<int64_t>(kPageTokens) * a.head_dim * elt;
-    const int64_t total = static_cast<int64_t>(a.n) * a.num_kv_heads * groups;
-    for (int64_t gi = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x; gi < total;
-         gi += static_cast<int64_t>(gridDim.x) * kBlockThreads) {
-        const int cd = static_cast<int>(gi % groups);
-        const int head = static_cast<int>((gi / groups) % a.num_kv_heads);
-        const int r = static_cast<int>(gi / (static_cast<int64_t>(groups) * a.num_kv_heads));
-        const AppendEntry e = a.n <= kAppendInline ? a.inline_entries[r] : a.entries[r];
-        char* lh = entry_slice(a.hot, a.cold, e.page, a.layer) + static_cast<int64_t>(head) * 2 * tile;
-        const int64_t src = ((static_cast<int64_t>(r) * a.num_kv_heads + head) * a.head_dim + cd * x) * elt;
-        write_token_group(lh, tile, e.slot, cd, x, elt, static_cast<const char*>(a.k) + src,
+    const int r = static_cast<int>(blockIdx.x);
+    const AppendEntry e = a.n <= kAppendInline ? a.inline_entries[r] : a.entries[r];
+    for (int t = static_cast<int>(threadIdx.x); t < a.num_kv_heads * groups; t += static_cast<int>(blockDim.x)) {
+        const AppendThread w = append_thread(t, groups);
+        char* lh = entry_slice(a.hot, a.cold, e.page, a.layer) + static_cast<int64_t>(w.head) * 2 * tile;
+        const int64_t src = ((static_cast<int64_t>(r) * a.num_kv_heads + w.head) * a.head_dim + w.cd * x) * elt;
+        write_token_group(lh, tile, e.slot, w.cd, x, elt, static_cast<const char*>(a.k) + src,
                           static_cast<const char*>(a.v) + src);
     }
 }
 
-// Appends whose page is resolved on the device: entry r writes token
-// positions[r] of batch row rows[r] for layers [layer, layer + num_layers),
-// into the page that row's page-table entry names (a hot page, or a spilled
-// page of the cold pool), at slot positions[r] % 16.  One thread per (layer,
-// entry, KV head, 16-byte group of dims).  An entry whose row, position or
+// Appends whose page is resolved on the device: entry blockIdx.x writes token
+// positions[r] of batch row rows[r] for layers [layer, layer +
+// num_layers), into the page that row's page-table entry names (a hot page, or a spilled page of the
+// cold pool), at slot positions[r] % 16.  An entry whose row, position or
 // page-table entry does not name a page of either pool writes nothing.
 __global__ __launch_bounds__(kBlockThreads) void append_table_kernel(const AppendTableArgs a) {
     const int elt = a.dtype == kDtypeBf16 ? 2 : 4;
     const int x = 16 / elt;
     const int groups = a.head_dim / x;
     const int64_t tile = static_cast<int64_t>(kPageTokens) * a.head_dim * elt;
-    const int64_t per_layer = static_cast<int64_t>(a.n) * a.num_kv_heads * groups;
-    const int64_t total = per_layer * a.num_layers;
-    for (int64_t gi = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x; gi < total;
-         gi += static_cast<int64_t>(gridDim.x) * kBlockThreads) {
-        const int li = static_cast<int>(gi / per_layer);
-        const int64_t wi = gi % per_layer;
-        const int cd = static_cast<int>(wi % groups);
-        const int head = static_cast<int>((wi / groups) % a.num_kv_heads);
-        const int r = static_cast<int>(wi / (static_cast<int64_t>(groups) * a.num_kv_heads));
-        const int32_t row = a.rows[r], pos = a.positions[r];
-        if (row < 0 || row >= a.table_rows || pos < 0 || pos / kPageTokens >= a.pt_stride) continue;
-        const int32_t pid = a.table[static_cast<int64_t>(row) * a.pt_stride + pos / kPageTokens];
-        const unsigned id = static_cast<unsigned>(pid) & static_cast<unsigned>(kPageIdMask);
-        const unsigned tag = static_cast<unsigned>(pid) >> 29;   // 0 hot, 2 cold; others name no page
-        if (!((tag == 0 && id < static_cast<unsigned>(a.num_hot)) ||
-              (tag == 2 && id < static_cast<unsigned>(a.num_cold))))
-            continue;
-        char* lh = entry_slice(a.hot, a.cold, pid, a.layer + li) + static_cast<int64_t>(head) * 2 * tile;
-        const int64_t src = (((static_cast<int64_t>(li) * a.n + r) * a.num_kv_heads + head) * a.head_dim + cd * x) * elt;
-        write_token_group(lh, tile, pos % kPageTokens, cd, x, elt, static_cast<const char*>(a.k) + src,
-                          static_cast<const char*>(a.v) + src);
+    const int r = static_cast<int>(blockIdx.x);
+    const int32_t row = a.rows[r], pos = a.positions[r];
+    if (row < 0 || row >= a.table_rows || pos < 0 || pos / kPageTokens >= a.pt_stride) return;
+    const int32_t pid = a.table[static_cast<int64_t>(row) * a.pt_stride + pos / kPageTokens];
+    const unsigned id = static_cast<unsigned>(pid) & static_cast<unsigned>(kPageIdMask);
+    const unsigned tag = static_cast<unsigned>(pid) >> 29;   // 0 hot, 2 cold; others name no page
+    if (!((tag == 0 && id < static_cast<unsigned>(a.num_hot)) || (tag == 2 && id < static_cast<unsigned>(a.num_cold))))
+        return;
+    for (int li = static_cast<int>(blockIdx.y); li < a.num_layers; li += static_cast<int>(gridDim.y)) {
+        for (int t = static_cast<int>(threadIdx.x); t < a.num_kv_heads * groups; t += static_cast<int>(blockDim.x)) {
+            const AppendThread w = append_thread(t, groups);
+            char* lh = entry_slice(a.hot, a.cold, pid, a.layer + li) + static_cast<int64_t>(w.head) * 2 * tile;
+            const int64_t src =
+                (((static_cast<int64_t>(li) * a.n + r) * a.num_kv_heads + w.head) * a.head_dim + w.cd * x) * elt;
+            write_token_group(lh, tile, pos % kPageTokens, w.cd, x, elt, static_cast<const char*>(a.k) + src,
+                              static_cast<const char*>(a.v) + src);
+        }
     }
 }
 
@@ -630,19 +639,25 @@ hipError_t launch_write_tokens(const WriteArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Threads of an append block: one per (KV head, 16-byte group) of a row, whole waves.
+unsigned append_threads(int num_kv_heads, int head_dim, int dtype) {
+    const int t = num_kv_heads * (head_dim / (dtype == kDtypeBf16 ? 8 : 4));
+    const int waves = (t + kWave - 1) / kWave * kWave;
+    return static_cast<unsigned>(waves < kBlockThreads ? waves : kBlockThreads);
+}
+
 hipError_t launch_append_tokens(const AppendArgs& a, hipStream_t s) {
-    const int x = a.dtype == kDtypeBf16 ? 8 : 4;
-    const int64_t work = static_cast<int64_t>(a.n) * a.num_kv_heads * (a.head_dim / x);
-    if (work <= 0) return hipSuccess;
-    hipLaunchKernelGGL(append_tokens_kernel, dim3(grid_for(work, 16384)), dim3(kBlockThreads), 0, s, a);
+    if (a.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(append_tokens_kernel, dim3(static_cast<unsigned>(a.n)),
+                       dim3(append_threads(a.num_kv_heads, a.head_dim, a.dtype)), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_append_table(const AppendTableArgs& a, hipStream_t s) {
-    const int x = a.dtype == kDtypeBf16 ? 8 : 4;
-    const int64_t work = static_cast<int64_t>(a.n) * a.num_kv_heads * (a.head_dim / x) * a.num_layers;
-    if (work <= 0) return hipSuccess;
-    hipLaunchKernelGGL(append_table_kernel, dim3(grid_for(work, 16384)), dim3(kBlockThreads), 0, s, a);
+    if (a.n <= 0 || a.num_layers <= 0) return hipSuccess;
+    const unsigned layers = a.num_layers < 65535 ? static_cast<unsigned>(a.num_layers) : 65535u;
+    hipLaunchKernelGGL(append_table_kernel, dim3(static_cast<unsigned>(a.n), layers),
+                       dim3(append_threads(a.num_kv_heads, a.head_dim, a.dtype)), 0, s, a);
     return hipGetLastError();
 }
 

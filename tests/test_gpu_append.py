@@ -146,3 +146,34 @@ def test_append_refuses_bad_rows_and_writes_nothing(dev):
     torch.cuda.synchronize()
     assert int(pool.hot.count_nonzero()) == 2 * 2 * 2 * 64 * 2
     pool.close()
+
+
+@pytest.mark.parametrize("dtype,D,hkv", [("bf16", 64, 1), ("bf16", 128, 16), ("f32", 64, 3), ("f32", 128, 16)])
+@pytest.mark.parametrize("n", [1, 256, 257])
+def test_append_blocks_of_every_width(dev, dtype, D, hkv, n):
+    """One block per row: less than a wave of threads per row, more than a block
+    (several rounds), KV heads that are no power of two, lists in the kernel
+    arguments and uploaded; host- and device-resolved appends write the bytes
+    that a plain write of the same tokens does."""
+    from paper_2609_25782_amd.pool import HotColdPool
+    lens = [int(x) for x in np.random.default_rng(n).integers(1, 40, size=n)]
+    total = sum(synth.pages_for(L) for L in lens)
+    pools = [HotColdPool(2, hkv, D, dtype, total, 0, n, 4) for _ in range(3)]
+    g = torch.Generator(device="cpu").manual_seed(n)
+    k, v = (torch.randn((2, n, hkv, D), generator=g).to(pools[0].torch_dtype).to(dev) for _ in range(2))
+    pos = [L - 1 for L in lens]
+    for p in pools:
+        p.hot.zero_()
+        for L in lens:
+            p.create_session(L)
+    for layer in range(2):
+        for b in range(n):
+            pools[0].write_tokens(b, layer, pos[b], k[layer, b:b + 1], v[layer, b:b + 1])
+        pools[1].append_tokens(layer, list(range(n)), pos, k[layer], v[layer])
+    ids = torch.arange(n, dtype=torch.int32, device=dev)
+    pools[2].append_tokens_table(0, pools[2].page_table, ids, torch.tensor(pos, dtype=torch.int32, device=dev), k, v)
+    torch.cuda.synchronize()
+    assert torch.equal(pools[1].hot, pools[0].hot)
+    assert torch.equal(pools[2].hot, pools[0].hot)
+    for p in pools:
+        p.close()
