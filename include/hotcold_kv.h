@@ -528,9 +528,8 @@ int kv_pool_set_decode_waves(kv_pool* pool, int32_t waves);
 
 enum kv_combine_mode {
     KV_COMBINE_SEPARATE = 0, /* partials merged by a second kernel (default) */
-    KV_COMBINE_FUSED = 1     /* the last wave of each (row, KV head) merges them; every
-                                wave's arrival is a device-scope release, which on gfx950
-                                writes back its L2, and this mode is slower */
+    KV_COMBINE_FUSED = 1     /* the last wave of each (row, KV head) merges them, through
+                                device-scope stores and loads; this mode is slower */
 };
 /* How paged_decode_attention merges its split partials.  The two modes merge
  * in different orders, so their results agree to float32 rounding, not bit for
@@ -664,8 +663,9 @@ int paged_decode_attention(kv_pool* pool, int32_t layer, const void* q, const in
  * a spilled page written in place), and then out[b] is the attention over
  * tokens [0, L), the new one included, exactly as paged_decode_attention would
  * give after a separate append.  The wave that reads the row's last page for a
- * KV head writes that head's part of the token first, so the append costs no
- * launch of its own and no extra pass: one kernel launch per layer serves a
+ * KV head takes that head's part of the token from k_new and v_new and stores it
+ * to the page meanwhile, so the append costs no launch of its own, no extra pass
+ * and no wait: one kernel launch per layer serves a
  * whole decode step's attention and KV append, and a serving step captured in
  * a HIP graph holds no append nodes.  A tail entry naming no page writes
  * nothing (and that row decodes to NaN, as in paged_decode_attention).  The

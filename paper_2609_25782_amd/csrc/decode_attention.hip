@@ -1552,8 +1552,9 @@ __global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void 
         store_quad<D, BF16>(a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad, res);
 }
 
-// Ring depth per shape: the deepest ring that still leaves two (or three)
-// waves per SIMD, i.e. at most 256 (168) VGPRs.
+// Ring depth per shape.  Deeper rings are no faster (bf16, 128 dims, layer
+// workload: 203 us with 3 pages, 205 with 4, 254 with 5, which spills; 64 dims:
+// 22.8 us with 5, 23 to 24.6 with 7 and 8), one of 2 pages is 11 us slower.
 template <int D, bool BF16>
 constexpr int ring_depth() {
     return BF16 ? (D == 128 ? HCK_RING_BF16_D128 : 5) : (D == 128 ? 2 : 3);
