@@ -424,7 +424,7 @@ __device__ void combine_segment(const DecodeArgs& a, int b, int g, int64_t u_a, 
         const int idx = it * kWave + lane;
         if (idx < items) {
             const int h = idx / kQuads, quad = idx % kQuads;
-            const f32x4 res = invalid ? f32x4{nan, nan, nan, nan} : BF16 ? acc[it] * (1.0f / den[it]) : acc[it] / den[it];
+            const f32x4 res = invalid ? f32x4{nan, nan, nan, nan} : acc[it] / den[it];
             store_quad<D, BF16>(a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad,
                                 res);
         }
@@ -728,12 +728,9 @@ __device__ __forceinline__ void finish_piece(const DecodeArgs& a, Held<D, BF16>&
     float l = wave_sum_4(st.l);
     if (bad) l = __builtin_nanf("");
     if (whole) {
-        // (o + 0) / l is what merging this one partial gives.  A head's lanes
-        // share l, so bf16 results take one division and multiply by it: the
-        // last float32 bit is far below bf16's rounding.
+        // (o + 0) / l is what merging this one partial gives
         if (word & kUnitRowInvalid) l = __builtin_nanf("");
-        const float inv = 1.0f / l;
-        auto val = [&](int c) { return BF16 ? (st.o[c] + 0.f) * inv : (st.o[c] + 0.f) / l; };
+        auto val = [&](int c) { return (st.o[c] + 0.f) / l; };
         if constexpr (HOLD) {
             held.row(a, b * a.num_kv_heads + g, lane, val);
         } else if (h < a.group) {
@@ -1546,7 +1543,7 @@ __global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void 
         const float nan = __builtin_nanf("");
         res = f32x4{nan, nan, nan, nan};
     } else {
-        res = BF16 ? acc * (1.0f / den) : acc / den;
+        res = acc / den;
     }
     if (grp == 0)
         store_quad<D, BF16>(a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad, res);

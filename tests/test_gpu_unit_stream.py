@@ -138,3 +138,34 @@ def test_rows_held_until_slots_fill(dev, dtype, D, hq, hkv, batch, waves):
     rows = [b for b in range(batch) if lens[b] and b != 7][:: max(1, batch // 300)]
     rowwise_check(got[rows], case.oracle_out(rows=rows), max_norm=1e-2 if dtype == "bf16" else 1e-5)
     assert np.isfinite(np.delete(got, 7, axis=0)).all()
+
+
+# 387 lies halfway between two bfloat16 values and is the mean of 386 and 388; for these
+# token counts the float32 product 387 n * (1 / n) falls below it, the quotient does not
+HALFWAY_LENS = [n for n in range(2, 1024, 2)
+                if np.float32(387 * n) * (np.float32(1) / np.float32(n)) < np.float32(387)]
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("group", [8, 2])          # rows held in LDS, rows stored as they end
+@pytest.mark.parametrize("waves", [4, 768])        # whole rows and merged partials
+def test_bf16_outputs_are_rounded_quotients(dev, group, waves, fused):
+    """Zero queries make every weight 1, so each output is a sum of small integers over
+    the token count, both exact in float32: 387, which rounds to even, 388.  A result one
+    float32 unit below 387 rounds to 386."""
+    from paper_2609_25782_amd.pool import HotColdPool
+    lens, D = HALFWAY_LENS, 64
+    assert len(lens) > 20
+    pages = [synth.pages_for(L) for L in lens]
+    pool = HotColdPool(1, 1, D, "bf16", sum(pages), 0, len(lens), max(pages))
+    for L in lens:
+        k = torch.zeros((L, 1, D), dtype=torch.bfloat16, device=dev)
+        v = torch.full_like(k, 386)
+        v[1::2] = 388
+        pool.write_tokens(pool.create_session(L), 0, 0, k, v)
+    pool.set_waves(waves)
+    pool.set_combine(fused)
+    q = torch.zeros((len(lens), group, D), dtype=torch.bfloat16, device=dev)
+    got = to_host(pool.decode(0, q, torch.tensor(lens, dtype=torch.int32, device=dev)))
+    pool.close()
+    assert (got == 388).all(), np.unique(got, return_counts=True)
