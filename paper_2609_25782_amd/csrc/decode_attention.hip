@@ -323,6 +323,14 @@ __device__ __forceinline__ void lse_merge(float& M, float& den, f32x4& acc, floa
     M = Mn;
 }
 
+// ceil-style worker of a unit: the worker that owns unit u - 1, for u >= 1.
+__device__ __forceinline__ int unit_worker(int64_t u, int workers, int64_t total) {
+    if (total * workers <= 0xFFFFFFFFll)
+        return static_cast<int>((static_cast<unsigned>(u) * static_cast<unsigned>(workers) - 1u) /
+                                static_cast<unsigned>(total));
+    return static_cast<int>((u * workers - 1) / total);
+}
+
 // Range of waves whose partials belong to segment (b, g): units [u_a, u_a + nb).
 struct SegWaves {
     int k_first, k_last, pieces;
@@ -337,9 +345,6 @@ __device__ __forceinline__ SegWaves seg_waves(int64_t u_a, int nb, int64_t T, in
     return w;
 }
 
-// One wave merges every query head of segment (b, g): lane l owns the items
-// (head, 4-dim quad) l, l + 64, ...; loads of all its items for one partial
-// are issued together.
 template <int D, bool BF16>
 __device__ __forceinline__ void store_quad(const DecodeArgs& a, int64_t orow, const f32x4& res) {
     if constexpr (BF16) {
@@ -363,72 +368,85 @@ __device__ void fill_segment(const DecodeArgs& a, int b, int g, float value, int
     }
 }
 
-template <int D, bool BF16>
-__device__ void combine_segment(const DecodeArgs& a, int b, int g, int64_t u_a, int nb, int64_t T,
-                                int lane) {
-    const PartialsRsrc pr(a);
+// One wave merges every query head of segment (b, g): an item is (head, 4-dim
+// quad), lane l takes items first + l + 64 it, in the order of the partials.  It
+// is bound by the latency of device-scope loads, so kItems x kBatch of them are
+// in flight together, and they are unconditional (past the end: the last item or
+// partial again, unused): under a condition each waited for the ones before it.
+// One row of 2K tokens (128 partials) 181 -> 65 us a call, 8 x 2K 50 -> 27 us;
+// the merge before the unit stream, four partials at a time, 147 and 42 us.
+template <int D, bool BF16, int kItems, int kBatch>
+__device__ __forceinline__ void merge_items(const DecodeArgs& a, const PartialsRsrc& pr, int b, int g, int64_t u_a,
+                                            int64_t T, int k_first, int count, int first, bool invalid, int lane) {
     constexpr int kQuads = D / 4;
-    constexpr int kMaxItems = (16 * kQuads + kWave - 1) / kWave;
-    constexpr int kBatch = 4;  // partials whose loads are in flight together
     const int items = a.group * kQuads;
     const int gw = a.group_waves;
     const int64_t sseg = static_cast<int64_t>(b) * (a.num_kv_heads / gw) + g / gw;
     const int w = g % gw;
     const int N = a.waves / gw;
-    // fewer workers than units: workers k_first.. each hold one piece; more:
-    // each unit is a piece, held by the worker that owns it
-    const bool per_unit = N > T;
-    const int k_first = static_cast<int>(((u_a + 1) * N - 1) / T);
-    const int count = per_unit ? nb : static_cast<int>(((u_a + nb) * N - 1) / T) - k_first + 1;
-    float M[kMaxItems], den[kMaxItems];
-    f32x4 acc[kMaxItems];
+    int h[kItems], quad[kItems];
+    float M[kItems], den[kItems];
+    f32x4 acc[kItems];
 #pragma unroll
-    for (int it = 0; it < kMaxItems; ++it) {
+    for (int it = 0; it < kItems; ++it) {
+        const int idx = first + it * kWave + lane < items ? first + it * kWave + lane : items - 1;
+        h[it] = idx / kQuads;
+        quad[it] = idx % kQuads;
         M[it] = -INFINITY;
         den[it] = 0.f;
         acc[it] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     for (int i0 = 0; i0 < count; i0 += kBatch) {
-        float mk[kBatch][kMaxItems], lk[kBatch][kMaxItems];
-        f32x4 ok[kBatch][kMaxItems];
+        // lane j: the worker of partial i0 + j.  With more workers than units each
+        // unit is a partial, held by the worker that owns it, else workers
+        // k_first.. hold one each.
+        const int i = i0 + lane < count ? i0 + lane : count - 1;
+        const int k = N > T ? unit_worker(u_a + i + 1, N, T) : k_first + i;
+        float mk[kBatch][kItems], lk[kBatch][kItems];
+        f32x4 ok[kBatch][kItems];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            const int i = i0 + j < count ? i0 + j : count - 1;  // past the end: reload the last, unused
-            const int k = per_unit ? static_cast<int>(((u_a + i + 1) * N - 1) / T) : k_first + i;
-            const int64_t slot = (static_cast<int64_t>(k) + sseg) * gw + w;
+            const int64_t slot = (static_cast<int64_t>(__builtin_amdgcn_readlane(k, j)) + sseg) * gw + w;
             const float* pml = a.part_ml + slot * 2 * a.group;
 #pragma unroll
-            for (int it = 0; it < kMaxItems; ++it) {
-                const int idx = it * kWave + lane;
-                if (idx < items) {
-                    const int h = idx / kQuads, quad = idx % kQuads;
-                    mk[j][it] = pr.load1(pml + h);
-                    lk[j][it] = pr.load1(pml + a.group + h);
-                    ok[j][it] = pr.load4(a.part_o + (slot * a.group + h) * D + 4 * quad);
-                }
+            for (int it = 0; it < kItems; ++it) {
+                mk[j][it] = pr.load1(pml + h[it]);
+                lk[j][it] = pr.load1(pml + a.group + h[it]);
+                ok[j][it] = pr.load4(a.part_o + (slot * a.group + h[it]) * D + 4 * quad[it]);
             }
         }
 #pragma unroll
         for (int j = 0; j < kBatch; ++j)
             if (i0 + j < count)
 #pragma unroll
-                for (int it = 0; it < kMaxItems; ++it)
-                    if (it * kWave + lane < items)
-                        lse_merge(M[it], den[it], acc[it], mk[j][it], lk[j][it], ok[j][it]);
+                for (int it = 0; it < kItems; ++it) lse_merge(M[it], den[it], acc[it], mk[j][it], lk[j][it], ok[j][it]);
     }
-    const int32_t len = a.seq_lens[b];
-    const bool invalid = static_cast<int64_t>(len) > kPageTokens * a.pt_stride;
     const float nan = __builtin_nanf("");
 #pragma unroll
-    for (int it = 0; it < kMaxItems; ++it) {
-        const int idx = it * kWave + lane;
-        if (idx < items) {
-            const int h = idx / kQuads, quad = idx % kQuads;
-            const f32x4 res = invalid ? f32x4{nan, nan, nan, nan} : acc[it] / den[it];
-            store_quad<D, BF16>(a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h) * D + 4 * quad,
-                                res);
-        }
-    }
+    for (int it = 0; it < kItems; ++it)
+        if (first + it * kWave + lane < items)
+            store_quad<D, BF16>(
+                a, (static_cast<int64_t>(b) * a.num_q_heads + g * a.group + h[it]) * D + 4 * quad[it],
+                invalid ? f32x4{nan, nan, nan, nan} : acc[it] / den[it]);
+}
+
+template <int D, bool BF16>
+__device__ void combine_segment(const DecodeArgs& a, int b, int g, int64_t u_a, int nb, int64_t T,
+                                int lane) {
+    const PartialsRsrc pr(a);
+    const int N = a.waves / a.group_waves;
+    const int k_first = unit_worker(u_a + 1, N, T);
+    const int count = N > T ? nb : unit_worker(u_a + nb, N, T) - k_first + 1;
+    const bool invalid = static_cast<int64_t>(a.seq_lens[b]) > kPageTokens * a.pt_stride;
+    // all of a segment's items together where that leaves several partials in flight
+    const int items = a.group * (D / 4);
+    if (items <= kWave)
+        merge_items<D, BF16, 1, 16>(a, pr, b, g, u_a, T, k_first, count, 0, invalid, lane);
+    else if (items <= 2 * kWave)
+        merge_items<D, BF16, 2, 8>(a, pr, b, g, u_a, T, k_first, count, 0, invalid, lane);
+    else
+        for (int first = 0; first < items; first += 4 * kWave)
+            merge_items<D, BF16, 4, 4>(a, pr, b, g, u_a, T, k_first, count, first, invalid, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1323,11 +1341,10 @@ __device__ void run_piece_valu(const DecodeArgs& a, const Piece& pc, int nb, int
 // Register budget of the split kernel: 512 / n registers, so that n waves fit a
 // SIMD.  With 256 the shapes below keep everything in VGPRs; with 512 the
 // compiler holds the accumulators in AGPRs and moves all of them in and out on
-// every page.  The float32 128-dim shape and the 128-dim fused forms need more
-// than 256.
-template <int D, bool BF16, bool FUSED>
+// every page.  The float32 128-dim shape needs more than 256.
+template <int D, bool BF16>
 constexpr int split_waves_per_eu() {
-    return D == 128 && (!BF16 || FUSED) ? 1 : 2;
+    return D == 128 && !BF16 ? 1 : 2;
 }
 
 // Dynamic LDS of the split: the row prefix, then (HOLD) what each wave holds.
@@ -1376,7 +1393,7 @@ __device__ __forceinline__ void fill_empty_rows(const DecodeArgs& a, const int32
 
 template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND, bool HOLD>
 __global__ __launch_bounds__(kSplitBlockThreads)
-__attribute__((amdgpu_waves_per_eu(split_waves_per_eu<D, BF16, FUSED>()))) void decode_split_kernel(DecodeArgs a) {
+__attribute__((amdgpu_waves_per_eu(split_waves_per_eu<D, BF16>()))) void decode_split_kernel(DecodeArgs a) {
     extern __shared__ int32_t s_pref[];
     WaveWork w;
     if (!wave_work(a, s_pref, w)) return;
@@ -1437,14 +1454,6 @@ __global__ __launch_bounds__(kSplitBlockThreads) void decode_split_valu_kernel(D
 // of 8 x 2K tokens, with the shorter prefix sum, 848 -> 804 us.
 constexpr int kWideCombinePieces = 12;   // partials per segment from which four waves share a head
 constexpr int kWidestCombinePieces = 64; // and sixteen
-
-// ceil-style worker of a unit: the worker that owns unit u - 1, for u >= 1.
-__device__ __forceinline__ int unit_worker(int64_t u, int workers, int64_t total) {
-    if (total * workers <= 0xFFFFFFFFll)
-        return static_cast<int>((static_cast<unsigned>(u) * static_cast<unsigned>(workers) - 1u) /
-                                static_cast<unsigned>(total));
-    return static_cast<int>((u * workers - 1) / total);
-}
 
 template <int D, bool BF16, int kWaves>
 __global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void decode_combine_kernel(DecodeArgs a) {

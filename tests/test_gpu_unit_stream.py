@@ -204,3 +204,23 @@ def test_fused_append_keeps_pages_in_flight(dev, tiered):
     plain, append = split_ms(), split_ms(k_new=q, v_new=q)
     pool.close()
     assert append < 1.3 * plain, (plain, append)
+
+
+@pytest.mark.parametrize("dtype,D,group", [
+    ("bf16", 64, 4), ("bf16", 64, 5), ("bf16", 128, 4), ("bf16", 128, 5), ("bf16", 128, 16), ("f32", 64, 16),
+    ("f32", 128, 1), ("f32", 128, 9)])
+@pytest.mark.parametrize("waves", [3, 17, 300, 1000])
+def test_fused_merge_of_every_width(dev, dtype, D, group, waves):
+    """Groups whose (head, 4-dim quad) items are 64, 128, 256 and more, so that the merging
+    wave takes 16, 8 and 4 partials at a time, of one row cut into fewer and more pieces
+    (one per page with more waves than pages), beside a whole short row."""
+    lens = [16 * 333 - 5, 7]
+    case = Case(1, group, 1, D, dtype, lens, seed=67)
+    pool = build_gpu(case, dev)
+    pool.set_waves(waves)
+    pool.set_combine(True)
+    q, sl = to_device(case.q, dtype, dev), torch.tensor(lens, dtype=torch.int32, device=dev)
+    outs = [to_host(pool.decode(0, q, sl)) for _ in range(3)]    # counters back at zero after each
+    pool.close()
+    rowwise_check(outs[0], case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
