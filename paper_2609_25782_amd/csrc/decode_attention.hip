@@ -1453,15 +1453,16 @@ __global__ __launch_bounds__(kSplitBlockThreads) void decode_split_valu_kernel(D
 // tokens (192 partials) 11.8 -> 6.9 us in this kernel, and a captured 48-layer step
 // of 8 x 2K tokens, with the shorter prefix sum, 848 -> 804 us.
 constexpr int kWideCombinePieces = 12;   // partials per segment from which four waves share a head
-constexpr int kWidestCombinePieces = 64; // and sixteen
+constexpr int kWidestCombinePieces = 64; // and sixteen: 63 partials of 128 dims 9.6 us a captured call with four
+                                         // waves, 9.3 with sixteen; 96 of 64 dims (float32) 10.6 and 10.3
+constexpr int kCombineUnroll = 4;        // partials a lane loads before it merges any
 
 template <int D, bool BF16, int kWaves>
 __global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void decode_combine_kernel(DecodeArgs a) {
     constexpr bool kWide = kWaves > 1;
     constexpr int kQuads = D / 4;
     constexpr int kGroups = kWave / kQuads;
-    constexpr int kUnroll = 4;
-    constexpr int kStride = kWaves * kGroups;
+    constexpr int kUnroll = kCombineUnroll;
     __shared__ float s_merge[kWaves][kQuads][6];
     const int wave = threadIdx.x / kWave;
     const int Lw = a.group_waves;
@@ -1505,15 +1506,21 @@ __global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void 
     const bool per_unit = N > T;  // every non-empty wave holds exactly one unit
     const int count = per_unit ? nb : unit_worker(u_a + nb, N, T) - k_first + 1;
     if (count == 1) return;
+    // Waves that get partials: as many as have kUnroll per lane group.  With the
+    // partials dealt to all sixteen, the fifteen merges through LDS cost more than
+    // the shorter loop saves (captured calls, one row of 1K tokens: 63 partials
+    // 9.7 -> 7.9 us a call with 64 dims, 10.6 -> 9.3 with 128; four waves took 8.2 and 10.9).
+    const int used = kWide ? min(kWaves, (count + kUnroll * kGroups - 1) / (kUnroll * kGroups)) : 1;
+    const int stride = used * kGroups;
     float M = -INFINITY, den = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (!invalid) {
-        for (int i0 = gid; i0 < count; i0 += kUnroll * kStride) {
+    if (!invalid && (!kWide || wave < used)) {
+        for (int i0 = gid; i0 < count; i0 += kUnroll * stride) {
             float mk[kUnroll], lk[kUnroll];
             f32x4 ok[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                const int i = i0 + u * kStride;
+                const int i = i0 + u * stride;
                 const bool use = i < count;
                 const int k = per_unit && use ? unit_worker(u_a + i + 1, N, T) : k_first + i;
                 const int64_t slot = (static_cast<int64_t>(use ? k : k_first) + sseg) * Lw + w_in;
@@ -1550,6 +1557,7 @@ __global__ __launch_bounds__(kWaves == 1 ? kBlockThreads : kWaves * kWave) void 
         if (wave != 0) return;
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) {
+            if (w >= used) break;  // uniform
             const float* e = s_merge[w][quad];
             lse_merge(M, den, acc, e[0], e[1], f32x4{e[2], e[3], e[4], e[5]});
         }
@@ -1679,7 +1687,12 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
         return hipErrorInvalidValue;
     // Many partials per segment (waves well above segments): several waves per head.
     const int64_t pieces = a.waves / segs;
-    const int per_head = pieces >= kWidestCombinePieces ? 16 : pieces >= kWideCombinePieces ? 4 : 1;
+    int per_head = pieces >= kWidestCombinePieces ? 16 : pieces >= kWideCombinePieces ? 4 : 1;
+    // A segment has at most a table row's pages as partials: no more waves than
+    // they give work to (the merge is the same, see `used` in the kernel).  Rows
+    // of one page, 2 KV heads of 64 dims: 6.3 us a call with sixteen waves, 5.7 with one.
+    const int per_wave = kCombineUnroll * 4 * kWave / head_dim;
+    while (per_head > 1 && a.pt_stride <= per_head / 4 * per_wave) per_head /= 4;
     const bool wide = per_head > 1;
     const void* k = pick_combine(head_dim, dtype, per_head);
     if (!k) return hipErrorInvalidValue;

@@ -224,3 +224,23 @@ def test_fused_merge_of_every_width(dev, dtype, D, group, waves):
     pool.close()
     rowwise_check(outs[0], case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("dtype,D,pages", [
+    (dtype, D, n) for dtype, D in (("bf16", 128), ("f32", 64)) for n in (1, 7, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 200)])
+def test_merge_is_the_same_for_every_table_stride(dev, dtype, D, pages):
+    """A row's partials are at most its table row's entries, and the merge takes no more
+    waves than those give work to: the same result, bit for bit, through a table that is
+    just wide enough and through a wide one."""
+    lens = [16 * pages - 3]
+    case = Case(1, 2, 1, D, dtype, lens, seed=71, extra_stride=0)
+    pool = build_gpu(case, dev)
+    q, sl = to_device(case.q, dtype, dev), torch.tensor(lens, dtype=torch.int32, device=dev)
+    outs = []
+    for stride in (pages, 16 * pages + 4000):
+        table = torch.full((1, stride), -1, dtype=torch.int32, device=dev)
+        table[:, :pages] = pool.page_table
+        outs.append(pool.decode(0, q, sl, page_table=table).clone())
+    pool.close()
+    assert torch.equal(outs[0], outs[1])
+    tolerance_check(to_host(outs[0]), case.oracle_out(), max_norm=1e-2 if dtype == "bf16" else 1e-5)
