@@ -350,8 +350,9 @@ int kv_write_tokens_layers(kv_pool* pool, int32_t sid, int32_t layer_begin, int3
 /*
  * Batched append for a decode step (data path 3, Sec. III): for one layer, row
  * i of k and v (device arrays [n][num_kv_heads][head_dim], pool dtype) is
- * token positions[i] of ACTIVE session sids[i] (host arrays, n <= 8192).  One
- * launch writes every row.  Call kv_session_extend first so the positions lie
+ * token positions[i] of ACTIVE session sids[i] (host arrays, n <= 8192).  k and
+ * v need the alignment of their elements only; at 16 bytes they are read in
+ * whole words.  One launch writes every row.  Call kv_session_extend first so the positions lie
  * inside the sessions.  A token on a spilled page is written to its cold page
  * in place; hot pages written to lose their cold copy, as with kv_write_tokens.
  * All rows are checked before anything is written or launched.  On a

@@ -307,12 +307,28 @@ __global__ __launch_bounds__(kBlockThreads) void fill_synthetic_kernel(SynthArgs
 // One 16-byte group of dims (x elements) of one token's K and V into the
 // (layer, KV head) slice `lh` of its page, token slot `slot`: K is a 16-byte
 // store (the group is contiguous in the K tile); V, dims-major and
-// token-minor, takes one element store per dim.
+// token-minor, takes one element store per dim.  `aligned`: both sources are
+// 16-byte aligned; else they are read element by element.
+__device__ __forceinline__ u32x4 load_group(const char* p, int elt, bool aligned) {
+    if (aligned) return *reinterpret_cast<const u32x4*>(p);
+    u32x4 w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (elt == 2) {
+            const unsigned short* e = reinterpret_cast<const unsigned short*>(p) + 2 * j;
+            w[j] = e[0] | static_cast<unsigned>(e[1]) << 16;
+        } else {
+            w[j] = reinterpret_cast<const unsigned*>(p)[j];
+        }
+    }
+    return w;
+}
+
 __device__ __forceinline__ void write_token_group(char* lh, int64_t tile, int slot, int cd, int x, int elt,
-                                                  const char* ksrc, const char* vsrc) {
+                                                  const char* ksrc, const char* vsrc, bool aligned) {
+    const u32x4 v = load_group(vsrc, elt, aligned);
     *reinterpret_cast<u32x4*>(lh + (static_cast<int64_t>(cd) * kPageTokens + slot) * x * elt) =
-        *reinterpret_cast<const u32x4*>(ksrc);
-    const u32x4 v = *reinterpret_cast<const u32x4*>(vsrc);
+        load_group(ksrc, elt, aligned);
     char* vt = lh + tile + (static_cast<int64_t>(cd) * x * kPageTokens + slot) * elt;
     if (elt == 2) {
 #pragma unroll
@@ -422,7 +438,8 @@ __device__ __forceinline__ AppendThread append_thread(int t, int groups) {
 }
 
 // Row blockIdx.x of the batch: one token into page e[r].page (a hot id, or a cold id
-// tagged KV_PAGE_COLD) at slot e[r].slot; K and V rows [n][kv_heads][head_dim].
+// tagged KV_PAGE_COLD) at slot e[r].slot; K and V rows [n][kv_heads][head_dim],
+// element-aligned.
 __global__ __launch_bounds__(kBlockThreads) void append_tokens_kernel(const AppendArgs a) {
     const int elt = a.dtype == kDtypeBf16 ? 2 : 4;
     const int x = 16 / elt;
@@ -430,12 +447,13 @@ __global__ __launch_bounds__(kBlockThreads) void append_tokens_kernel(const Appe
     const int64_t tile = static_cast<int64_t>(kPageTokens) * a.head_dim * elt;
     const int r = static_cast<int>(blockIdx.x);
     const AppendEntry e = a.n <= kAppendInline ? a.inline_entries[r] : a.entries[r];
+    const bool aligned = ((reinterpret_cast<uintptr_t>(a.k) | reinterpret_cast<uintptr_t>(a.v)) & 15) == 0;
     for (int t = static_cast<int>(threadIdx.x); t < a.num_kv_heads * groups; t += static_cast<int>(blockDim.x)) {
         const AppendThread w = append_thread(t, groups);
         char* lh = entry_slice(a.hot, a.cold, e.page, a.layer) + static_cast<int64_t>(w.head) * 2 * tile;
         const int64_t src = ((static_cast<int64_t>(r) * a.num_kv_heads + w.head) * a.head_dim + w.cd * x) * elt;
         write_token_group(lh, tile, e.slot, w.cd, x, elt, static_cast<const char*>(a.k) + src,
-                          static_cast<const char*>(a.v) + src);
+                          static_cast<const char*>(a.v) + src, aligned);
     }
 }
 
@@ -464,7 +482,7 @@ __global__ __launch_bounds__(kBlockThreads) void append_table_kernel(const Appen
             const int64_t src =
                 (((static_cast<int64_t>(li) * a.n + r) * a.num_kv_heads + w.head) * a.head_dim + w.cd * x) * elt;
             write_token_group(lh, tile, pos % kPageTokens, w.cd, x, elt, static_cast<const char*>(a.k) + src,
-                              static_cast<const char*>(a.v) + src);
+                              static_cast<const char*>(a.v) + src, true);
         }
     }
 }

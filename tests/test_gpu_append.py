@@ -177,3 +177,27 @@ def test_append_blocks_of_every_width(dev, dtype, D, hkv, n):
     assert torch.equal(pools[2].hot, pools[0].hot)
     for p in pools:
         p.close()
+
+
+@pytest.mark.parametrize("dtype,D,hkv,n", [("bf16", 64, 1, 3), ("bf16", 128, 4, 300), ("f32", 64, 3, 7), ("f32", 128, 16, 2)])
+@pytest.mark.parametrize("k_off,v_off", [(0, 1), (1, 0), (3, 3)])
+def test_append_reads_tokens_at_any_element(dev, dtype, D, hkv, n, k_off, v_off):
+    """k and v as views that start some elements into a buffer, so that rows are not 16-byte
+    aligned: the bytes written are those of aligned copies."""
+    from paper_2609_25782_amd.pool import HotColdPool
+    g = torch.Generator(device="cpu").manual_seed(n)
+    pools = [HotColdPool(1, hkv, D, dtype, n, 0, n, 1) for _ in range(2)]
+    flat = [torch.randn(n * hkv * D + 8, generator=g).to(pools[0].torch_dtype).to(dev) for _ in range(2)]
+    k, v = (t[o:o + n * hkv * D].view(n, hkv, D) for t, o in zip(flat, (k_off, v_off)))
+    assert (k.data_ptr() | v.data_ptr()) % 16
+    pos = [i % 16 for i in range(n)]
+    for p, kk, vv in ((pools[0], k.clone(), v.clone()), (pools[1], k, v)):
+        p.hot.zero_()
+        for _ in range(n):
+            p.create_session(16)
+        p.append_tokens(0, list(range(n)), pos, kk, vv)
+    torch.cuda.synchronize()
+    assert int(pools[0].hot.count_nonzero()) > 0
+    assert torch.equal(pools[0].hot, pools[1].hot)
+    for p in pools:
+        p.close()
