@@ -151,8 +151,8 @@ def test_append_refuses_bad_rows_and_writes_nothing(dev):
 @pytest.mark.parametrize("dtype,D,hkv", [("bf16", 64, 1), ("bf16", 128, 16), ("f32", 64, 3), ("f32", 128, 16)])
 @pytest.mark.parametrize("n", [1, 256, 257])
 def test_append_blocks_of_every_width(dev, dtype, D, hkv, n):
-    """One block per row: less than a wave of threads per row, more than a block
-    (several rounds), KV heads that are no power of two, lists in the kernel
+    """One block per row: less than a wave of threads per row, the widest block,
+    KV heads that are no power of two, lists in the kernel
     arguments and uploaded; host- and device-resolved appends write the bytes
     that a plain write of the same tokens does."""
     from paper_2609_25782_amd.pool import HotColdPool
