@@ -1365,7 +1365,9 @@ constexpr int split_waves_per_eu() {
     return D == 128 && !BF16 ? 1 : 2;
 }
 
-// Dynamic LDS of the split: the row prefix, then (HOLD) what each wave holds.
+// Dynamic LDS of the split: the row prefix, then (HOLD) what each wave holds, in
+// 16-byte words: the array is declared with that alignment, which otherwise would
+// depend on the sizes of the static arrays before it.
 __host__ __device__ __forceinline__ int prefix_lds_bytes(int batch) { return (4 * (batch + 1) + 15) & ~15; }
 
 template <int D>
@@ -1412,7 +1414,8 @@ __device__ __forceinline__ void fill_empty_rows(const DecodeArgs& a, const int32
 template <int D, bool BF16, int R, bool TIERED, bool FUSED, bool APPEND, bool HOLD>
 __global__ __launch_bounds__(kSplitBlockThreads)
 __attribute__((amdgpu_waves_per_eu(split_waves_per_eu<D, BF16>()))) void decode_split_kernel(DecodeArgs a) {
-    extern __shared__ int32_t s_pref[];
+    extern __shared__ __align__(16) int32_t s_pref[];
+    static_assert(__alignof__(s_pref) >= 16, "Held reads and writes 16-byte words behind the prefix");
     WaveWork w;
     if (!wave_work(a, s_pref, w)) return;
     const SplitEnds ends = run_units<D, BF16, R, TIERED, FUSED, APPEND, HOLD>(
@@ -1429,7 +1432,7 @@ __attribute__((amdgpu_waves_per_eu(split_waves_per_eu<D, BF16>()))) void decode_
 // The vector-ALU form walks its range piece by piece.
 template <int D, int R, bool TIERED>
 __global__ __launch_bounds__(kSplitBlockThreads) void decode_split_valu_kernel(DecodeArgs a) {
-    extern __shared__ int32_t s_pref[];
+    extern __shared__ __align__(16) int32_t s_pref[];
     __shared__ ValuLds<D> s_valu[kSplitBlockWaves];
     WaveWork w;
     if (!wave_work(a, s_pref, w)) return;
