@@ -331,18 +331,10 @@ __device__ __forceinline__ int unit_worker(int64_t u, int workers, int64_t total
     return static_cast<int>((u * workers - 1) / total);
 }
 
-// Range of waves whose partials belong to segment (b, g): units [u_a, u_a + nb).
-struct SegWaves {
-    int k_first, k_last, pieces;
-};
-
-__device__ __forceinline__ SegWaves seg_waves(int64_t u_a, int nb, int64_t T, int N) {
-    SegWaves w;
-    w.k_first = static_cast<int>(((u_a + 1) * N - 1) / T);
-    w.k_last = static_cast<int>(((u_a + nb) * N - 1) / T);
-    // with more waves than units every non-empty wave holds exactly one unit
-    w.pieces = (N <= T) ? (w.k_last - w.k_first + 1) : nb;
-    return w;
+// Partials of a segment of units [u_a, u_a + nb): one per worker that holds some
+// of them, or one per unit with more workers than units.
+__device__ __forceinline__ int seg_pieces(int64_t u_a, int nb, int64_t T, int N) {
+    return N > T ? nb : unit_worker(u_a + nb, N, T) - unit_worker(u_a + 1, N, T) + 1;
 }
 
 template <int D, bool BF16>
@@ -436,7 +428,7 @@ __device__ void combine_segment(const DecodeArgs& a, int b, int g, int64_t u_a, 
     const PartialsRsrc pr(a);
     const int N = a.waves / a.group_waves;
     const int k_first = unit_worker(u_a + 1, N, T);
-    const int count = N > T ? nb : unit_worker(u_a + nb, N, T) - k_first + 1;
+    const int count = seg_pieces(u_a, nb, T, N);
     const bool invalid = static_cast<int64_t>(a.seq_lens[b]) > kPageTokens * a.pt_stride;
     // all of a segment's items together where that leaves several partials in flight
     const int items = a.group * (D / 4);
@@ -823,12 +815,12 @@ __device__ void merge_ends(const DecodeArgs& a, const int32_t* s_pref, const Spl
         const int b = seg / heads, hg = seg % heads, g = hg * a.group_waves + w_in;
         const int nb = lds_uniform(s_pref + b + 1) - lds_uniform(s_pref + b);
         const int64_t seg_first = static_cast<int64_t>(lds_uniform(s_pref + b)) * heads + static_cast<int64_t>(hg) * nb;
-        const SegWaves sw = seg_waves(seg_first, nb, total_units, a.waves / a.group_waves);
+        const int pieces = seg_pieces(seg_first, nb, total_units, a.waves / a.group_waves);
         int32_t* cnt = a.counters + b * a.num_kv_heads + g;
         int prev = 0;
         if (lane == 0) prev = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         prev = __builtin_amdgcn_readfirstlane(__shfl(prev, 0));
-        if (prev + 1 == sw.pieces) {
+        if (prev + 1 == pieces) {
             combine_segment<D, BF16>(a, b, g, seg_first, nb, total_units, lane);
             if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next call
         }
@@ -1156,10 +1148,10 @@ __device__ __forceinline__ void compute_page_valu(ValuState<D>& st, PageRegs<D, 
 // its own loads of the page (the same wave is the only reader of that page's
 // tiles for this KV head in the launch).  Rows with L <= 0 or an invalid L, and
 // tail entries that name no page (or a staging slot), write nothing.
-template <int D, bool BF16, bool TIERED>
+template <int D, bool TIERED>
 __device__ __forceinline__ void append_new_token(const DecodeArgs& a, const PageSrc& ps, const int32_t* row,
                                                  const Piece& pc, int nb, int seq_len, int lane) {
-    using S = Shape<D, BF16>;
+    using S = Shape<D, true>;
     if (!a.k_new || pc.p1 != nb || seq_len <= 0 || a.seq_lens[pc.b] != seq_len) return;
     unsigned id = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(row[nb - 1]));
     const char* base = ps.hot;
@@ -1188,10 +1180,7 @@ __device__ __forceinline__ void append_new_token(const DecodeArgs& a, const Page
             *reinterpret_cast<const u32x4*>(ks + 16 * lane);
     for (int d = lane; d < D; d += kWave) {
         char* vd = lh + S::kTile + (static_cast<int64_t>(d) * kPageTokens + slot) * S::kElt;
-        if constexpr (BF16)
-            *reinterpret_cast<unsigned short*>(vd) = reinterpret_cast<const unsigned short*>(vs)[d];
-        else
-            *reinterpret_cast<unsigned*>(vd) = reinterpret_cast<const unsigned*>(vs)[d];
+        *reinterpret_cast<unsigned short*>(vd) = reinterpret_cast<const unsigned short*>(vs)[d];
     }
     // Other lanes of this wave read these bytes back with the page's loads.  A
     // workgroup-scope release/acquire orders that in the memory model; waiting
@@ -1260,7 +1249,7 @@ __device__ void run_piece_valu(const DecodeArgs& a, const Piece& pc, int nb, int
         ps.num_cold = static_cast<unsigned>(a.num_cold_pages);
         ps.num_stage = static_cast<unsigned>(a.num_stage_slots);
     }
-    append_new_token<D, true, TIERED>(a, ps, row, pc, nb, seq_len, lane);
+    append_new_token<D, TIERED>(a, ps, row, pc, nb, seq_len, lane);
     const int qg = lane >> 4;
     const unsigned koff = 16u * lane;
     const unsigned voff = 32u * (lane & 15) + 8u * qg;
@@ -1728,16 +1717,6 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
                           ? dim3(static_cast<unsigned>(a.waves / a.group_waves), ny * a.group_waves)
                           : dim3(static_cast<unsigned>(segs), ny);
     return launch_kernel(k, grid, dim3(wide ? per_head * kWave : kBlockThreads), args, 0, s, ev);
-}
-
-int decode_split_blocks_per_cu(int head_dim, int dtype, int batch) {
-    const void* k = pick_split(head_dim, dtype, false, false, false, Merge::kSeparate);
-    if (!k) return 0;
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kSplitBlockThreads, prefix_lds_bytes(batch)) !=
-        hipSuccess)
-        return 0;
-    return n;
 }
 
 }  // namespace hck

@@ -73,8 +73,9 @@ struct DecodeArgs {
     int64_t slice_bytes;      // bytes of one staging slot
     int32_t out_slots;        // finished rows a wave holds in LDS (set by the split launch)
     int32_t valu;             // 1: the split runs its products on the vector ALU (bf16, group <= 8)
-    // Fused append (nullable): row b's token L - 1, [batch][num_kv_heads][head_dim], written
-    // into its page before the page is read.
+    // Fused append (nullable): row b's token L - 1, [batch][num_kv_heads][head_dim], stored
+    // to its page and attended to in the page's place (the vector-ALU form stores it first
+    // and reads the page back).
     const void* k_new;
     const void* v_new;
 };
@@ -143,8 +144,6 @@ hipError_t launch_decode_combine(const DecodeArgs& a, int head_dim, int dtype, h
                                  const LaunchEvents& ev = {});
 // Largest batch the decode kernels accept (bounds the counter array).
 constexpr int kMaxDecodeBatch = 8192;
-// Resident 256-thread blocks per CU of the split kernel (0 if unsupported shape).
-int decode_split_blocks_per_cu(int head_dim, int dtype, int batch);
 
 // (waves + batch * num_kv_heads) records of 4 int32: (b, g, first page, end page).
 hipError_t launch_gather_rows(const int32_t* pt, int64_t stride, int32_t max_sessions,

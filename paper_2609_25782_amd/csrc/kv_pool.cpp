@@ -417,11 +417,12 @@ struct kv_pool {
                                       copy_blocks, s, ev);
             prof_done(kernel_id, ev, e);
             if (e != hipSuccess) return hip_fail(e, "page copy launch");
-            if (!own_event) {
-                rc = release_slot(slot, s);
-                if (rc) return rc;
+            if (own_event) {
+                slot->pending = true;
+                continue;
             }
-            slot->pending = true;
+            rc = release_slot(slot, s);
+            if (rc) return rc;
         }
         return KV_OK;
     }
