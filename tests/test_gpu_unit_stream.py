@@ -277,3 +277,60 @@ def test_fused_append_waits_for_no_page_but_its_own(dev):
     pool.close()
     plain, append = min(t[0] for t in turns), min(t[1] for t in turns)
     assert append < 1.05 * plain, (plain, append)
+
+
+@pytest.mark.parametrize("dtype,D,hq,hkv", [
+    ("bf16", 128, 32, 4), ("bf16", 64, 16, 2), ("f32", 128, 8, 1), ("f32", 64, 8, 2)])
+@pytest.mark.parametrize("waves", [3, 4, 8])
+@pytest.mark.parametrize("append", [False, True])
+def test_rows_held_of_hot_and_spilled_pages(dev, dtype, D, hq, hkv, waves, append):
+    """Held rows over both tiers: every third row spilled, some of its pages promoted again,
+    so that a wave's chunk goes from hot pages to spilled ones and back, between rows and
+    inside one.  Against the oracle, and with the append bit for bit against a separate
+    append, the pages of both tiers included."""
+    rng = np.random.default_rng(10 * waves + D)
+    lens = [int(x) for x in rng.integers(1, 120, size=90)]
+    lens[4] = lens[5] = 0
+    lens[30] = 16 * 70 - 3    # a spilled row longer than a chunk
+    case = Case(1, hq, hkv, D, dtype, lens, seed=73)
+    q, sl = to_device(case.q, dtype, dev), torch.tensor(lens, dtype=torch.int32, device=dev)
+    rows = [b for b, L in enumerate(lens) if L]
+    new = [np.zeros((len(lens), hkv, D), case.kv[0][0].dtype) for _ in range(2)]
+    for b in rows:
+        for i in range(2):
+            new[i][b] = case.kv[b][i][lens[b] - 1]
+    kn, vn = (to_device(t, dtype, dev) for t in new)
+    nan = torch.full((1, hkv, D), float("nan"), dtype=kn.dtype, device=dev)
+    outs, pages = [], []
+    for form in ("fused", "separate") if append else ("plain",):
+        pool = build_gpu(case, dev, num_cold_pages=case.hot_pages, poison=True)
+        pool.cold.zero_()
+        pool.set_waves(waves)
+        pool.set_spill(True)
+        if append:    # the last token's slot holds NaN until it is appended
+            for b in rows:
+                pool.write_tokens(b, 0, lens[b] - 1, nan, nan)
+        spilled = [b for b in rows if b % 3 == 0]
+        pool.evict(spilled)
+        pool.resume_lazy(spilled)
+        assert pool.promote(sum(synth.pages_for(lens[b]) for b in spilled) // 2 + 1) > 0
+        tier = (pool.page_table >> 29).cpu().numpy()
+        mixed = [b for b in rows if len(set(tier[b, :synth.pages_for(lens[b])])) > 1]
+        assert mixed and (tier == 2).any() and (tier == 0).any()
+        out = torch.full_like(q, float("nan"))
+        if form == "fused":
+            pool.decode(0, q, sl, out=out, k_new=kn, v_new=vn)
+        else:
+            if form == "separate":
+                pool.append_tokens(0, rows, [lens[b] - 1 for b in rows], kn[rows].contiguous(), vn[rows].contiguous())
+            pool.decode(0, q, sl, out=out)
+        torch.cuda.synchronize()
+        outs.append(out)
+        pages.append((pool.hot.clone(), pool.cold.clone()))
+        pool.close()
+    got = to_host(outs[0])
+    assert (got[4:6] == 0).all()
+    rowwise_check(got[rows], case.oracle_out(rows=rows), max_norm=1e-2 if dtype == "bf16" else 1e-5)
+    if append:
+        assert torch.equal(outs[0], outs[1])
+        assert torch.equal(pages[0][0], pages[1][0]) and torch.equal(pages[0][1], pages[1][1])
