@@ -537,11 +537,18 @@ __device__ __forceinline__ UnitChunk load_units(const DecodeArgs& a, const int32
     return c;
 }
 
-// A chunk's loads are waited for here.  Without this the first use in the page loop
-// waits, in every round of the ring and so, from the second on, for nearly all
-// pages in flight: one layer of 8 x 2K tokens, 16 heads of 64 dims, 17.6 us a call,
-// now 16.6; 32 rows of 8K-32K, spilled pages and the append 431, now 404.
-__device__ __forceinline__ void settle(UnitChunk& c) { __asm__ volatile("" : "+v"(c.pid), "+v"(c.len)); }
+// Of 64-dim pages, a chunk's loads are waited for here.  Without this the first use
+// in the page loop waits, in every round of the ring and so, from the second on,
+// for nearly all pages in flight: one layer of 8 x 2K tokens, 16 heads of 64 dims,
+// 17.6 us a call, now 16.6; 32 rows of 8K-32K, spilled pages and the append 431, now
+// 404.  Pages of 128 dims keep the wait in the loop: they are twice as large, a round is
+// two or three of them, and long rows stream slightly faster with fewer in flight
+// (128 rows of 1K-256K, 32 query and 4 KV heads: 1,859 us a call with the wait in the
+// loop, 1,871 here).
+template <int D>
+__device__ __forceinline__ void settle(UnitChunk& c) {
+    if constexpr (D == 64) __asm__ volatile("" : "+v"(c.pid), "+v"(c.len));
+}
 
 // The V part of a row's new token (fused append): the element of each 16-dim
 // chunk that the lane's V registers of the tail page take.
@@ -834,8 +841,8 @@ __device__ void merge_ends(const DecodeArgs& a, const int32_t* s_pref, const Spl
 // row's output, not a drained ring.  Every step issues exactly one page's loads
 // (past the end with a resource of no records, which fetches nothing) and the
 // loops have no exit inside a round of R steps, so that the compiler's waits
-// count just the pages ahead: with the loads under a condition, as with an
-// early exit, they waited for nearly all of them.  A piece's queries, and the V
+// for a page count just the pages ahead: with the loads under a condition, as with
+// an early exit, they waited for nearly all of them (a chunk's list: see settle).  A piece's queries, and the V
 // of a tail page's new token (fused append), are loaded ahead of their page into
 // one set of registers each; where rows are so short that the set is still in
 // use, they are loaded when their page is computed.
@@ -985,7 +992,7 @@ __device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_
 
     UnitPos at = unit_pos(s_pref, a.batch, heads, u0, lane);
     UnitChunk nxt = load_units<kChunk>(a, s_pref, heads, at, u1 - u0, true, lane);
-    settle(nxt);
+    settle<D>(nxt);
     // steps left: every unit is issued once and computed R - 1 steps later
     for (int64_t left = u1 - u0 + (R - 1); left > 0; left -= kChunk) {
         const UnitChunk cur = nxt;
@@ -999,7 +1006,7 @@ __device__ __forceinline__ SplitEnds run_units(const DecodeArgs& a, const int32_
                 compute((r + 1) % R);
             }
         }
-        settle(nxt);
+        settle<D>(nxt);
     }
     if constexpr (HOLD) held.write_all(a, lane);
     return ends;
