@@ -653,9 +653,10 @@ __device__ __forceinline__ void wave_lds_sync() { __asm__ volatile("s_waitcnt lg
 // wave keeps the rows that it finishes in LDS, `out_slots` of them, and writes
 // them together, as full 1 KiB stores, when the slots are full and when its
 // range ends; the partial of the segment that its range starts inside of waits
-// for the end too.  1,024 rows of 512 tokens: 186.7 -> 167.8 us a call, of 256 to
-// 768 tokens 189 -> 168 us, of 1,500 on average 498 -> 466 us (6.9 TB/s); 512
-// rows of 8 KV heads, 512 tokens on average, 183 -> 177 us; float32 192 -> 182 us.
+// for the end too.  1,024 rows of 512 tokens: 186.7 -> 168.4 us a call (on other
+// cards 177), of 256 to 768 tokens 189 -> 168 us, of 1,500 on average 498 -> 466 us
+// (6.9 TB/s); 512 rows of 8 KV heads, 512 tokens on average, 183 -> 177 us; float32
+// 192 -> 182 us.
 constexpr int kLdsBudget = 60 << 10;  // of a 64 KiB launch, a few words of it static
 constexpr int kMaxOutSlots = 8;
 template <int D>
@@ -1468,7 +1469,8 @@ __global__ __launch_bounds__(kSplitBlockThreads) void decode_split_valu_kernel(D
 // always holds) and giving long segments sixteen waves took the float32
 // call of 16 ragged rows (48 partials each) from 25.0 to 23.1 us, one row of 32K
 // tokens (192 partials) 11.8 -> 6.9 us in this kernel, and a captured 48-layer step
-// of 8 x 2K tokens, with the shorter prefix sum, 848 -> 804 us.
+// of 8 x 2K tokens, with the shorter prefix sum, 848 -> 804 us (775 with the waves
+// that `used` counts below and the append's waits gone).
 constexpr int kWideCombinePieces = 12;   // partials per segment from which four waves share a head
 constexpr int kWidestCombinePieces = 64; // and sixteen: 63 partials of 128 dims 9.6 us a captured call with four
                                          // waves, 9.3 with sixteen; 96 of 64 dims (float32) 10.6 and 10.3
